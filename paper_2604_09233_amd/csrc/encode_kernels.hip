@@ -73,41 +73,48 @@ __device__ __forceinline__ int term_shift(const unsigned* __restrict__ tmax, int
   return (ea - eh) / 2;
 }
 
-// largest |a_b| (side 0, before the 1/2pi scaling) and |h_b| (side 1) per
-// term; grid (kTmaxBlocks, 2), one atomic max per term per workgroup
+// largest |a_b| (samples, before the 1/2pi scaling) and |h_b| (voxels) per
+// term; kTmaxSampBlocks workgroups for the samples, then kTmaxVoxBlocks for
+// every voxel row, one atomic max per term and workgroup.  Bound by the
+// reads: the row-major kcoef is walked as a flat array by threads that stay
+// on one column (a stride of whole rows), so neighbouring lanes read
+// neighbouring words (one row per lane, 64 bytes apart, on 64 workgroups
+// took 20 us at 60 000 x 16 and 200 us at 572 000 x 16).
 __global__ __launch_bounds__(256) void term_absmax_kernel(const float* __restrict__ t, const float* __restrict__ kcoef,
                                                           int64_t K, const float* __restrict__ b0,
                                                           const float* __restrict__ fields, int64_t L, int P,
                                                           unsigned* __restrict__ tmax) {
-  const int side = blockIdx.y;
-  const int64_t n = side == 0 ? K : L;
-  const float* c0 = side == 0 ? t : b0;
-  float mx[kMaxTerms];
-#pragma unroll
-  for (int b = 0; b < kMaxTerms; ++b) mx[b] = 0.f;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
-    mx[0] = fmaxf(mx[0], fabsf(c0[i]));
-#pragma unroll
-    for (int b = 1; b < kMaxTerms; ++b)
-      if (b <= P) {
-        const float v = side == 0 ? kcoef[i * P + (b - 1)] : fields[(int64_t)(b - 1) * L + i];
-        mx[b] = fmaxf(mx[b], fabsf(v));
-      }
-  }
-  __shared__ float red[kWaves][kMaxTerms];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int b = 0; b < kMaxTerms; ++b) {
-    float v = mx[b];
-    for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off));
-    if (lane == 0) red[wave][b] = v;
+  const int tid = threadIdx.x;
+  __shared__ unsigned red[kMaxTerms];
+  if (tid < kMaxTerms) red[tid] = 0u;
+  __syncthreads();
+  auto strided_max = [](const float* f, int64_t i, int64_t end, int64_t st) {
+    float m0 = 0.f, m1 = 0.f, m2 = 0.f, m3 = 0.f;
+    for (; i + 3 * st < end; i += 4 * st) {
+      m0 = fmaxf(m0, fabsf(f[i]));
+      m1 = fmaxf(m1, fabsf(f[i + st]));
+      m2 = fmaxf(m2, fabsf(f[i + 2 * st]));
+      m3 = fmaxf(m3, fabsf(f[i + 3 * st]));
+    }
+    for (; i < end; i += st) m0 = fmaxf(m0, fabsf(f[i]));
+    return fmaxf(fmaxf(m0, m1), fmaxf(m2, m3));
+  };
+  const int side = blockIdx.x >= kTmaxSampBlocks;
+  const int vb = blockIdx.x - kTmaxSampBlocks, row = side ? vb / kTmaxVoxBlocks : 0;
+  const float* f = side == 0 ? t : row == 0 ? b0 : fields + (int64_t)(row - 1) * L;
+  const int64_t blk = side ? vb % kTmaxVoxBlocks : blockIdx.x, nblk = side ? kTmaxVoxBlocks : kTmaxSampBlocks;
+  float mx = strided_max(f, blk * 256 + tid, side ? L : K, nblk * 256);
+  for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+  if ((tid & 63) == 0 && mx > 0.f) atomicMax(&red[row], __float_as_uint(mx));
+  if (side == 0 && P > 0) {
+    const int per = 256 / P * P;  // whole rows per workgroup and step
+    if (tid < per) {
+      const float m = strided_max(kcoef, blk * per + tid, K * P, nblk * per);
+      if (m > 0.f) atomicMax(&red[tid % P + 1], __float_as_uint(m));
+    }
   }
   __syncthreads();
-  if ((int)threadIdx.x <= P) {
-    float v = red[0][threadIdx.x];
-    for (int w = 1; w < kWaves; ++w) v = fmaxf(v, red[w][threadIdx.x]);
-    if (v > 0.f) atomicMax(&tmax[side * kMaxTerms + threadIdx.x], __float_as_uint(v));
-  }
+  if (tid <= P && red[tid]) atomicMax(&tmax[side * kMaxTerms + tid], red[tid]);
 }
 
 // side 0: samples (t, kcoef, K items); side 1: voxels (b0, fields, L items)
@@ -976,7 +983,7 @@ hipError_t launch_term_absmax(const float* t, const float* kcoef, int64_t K, con
                               int64_t L, int P, unsigned* tmax, hipStream_t s) {
   hipError_t e = launch_fill_zero((float*)tmax, 2 * kMaxTerms, s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(term_absmax_kernel, dim3(kTmaxBlocks, 2), dim3(256), 0, s, t, kcoef, K, b0, fields, L, P, tmax);
+  hipLaunchKernelGGL(term_absmax_kernel, dim3(kTmaxSampBlocks + (P + 1) * kTmaxVoxBlocks), dim3(256), 0, s, t, kcoef, K, b0, fields, L, P, tmax);
   return hipGetLastError();
 }
 

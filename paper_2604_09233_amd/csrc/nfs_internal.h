@@ -28,7 +28,8 @@ constexpr int kWaves = 4;         // waves per workgroup in the encode kernels
 constexpr int kCgBlocks = 256;    // max workgroups of the CG vector kernels
 constexpr int kBmaxBlocks = 256;  // workgroups of the max-magnitude kernels
 constexpr int kMaxTerms = 32;     // phase terms (t*b0 plus up to 31 field terms)
-constexpr int kTmaxBlocks = 64;   // workgroups per side of the term-maxima kernel
+// workgroups of the term-maxima kernel: for the samples, and per voxel row
+constexpr int kTmaxSampBlocks = 256, kTmaxVoxBlocks = 32;
 // Largest phase bound (revolutions) for which the hardware sine and cosine
 // take the phase directly; above it the argument is first reduced with
 // v_fract.  The hardware range is +-256 revolutions; the margin covers the
