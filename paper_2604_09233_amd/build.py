@@ -18,11 +18,12 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 BUILD_DIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libnfs.so")
-SOURCES = ["encode_kernels.hip", "cg_kernels.hip", "quality_kernels.hip", "postproc_kernels.hip", "maps_kernels.hip",
+SOURCES = ["encode_kernels.hip", "grad_kernels.hip", "cg_kernels.hip", "quality_kernels.hip", "postproc_kernels.hip", "maps_kernels.hip",
            "compress_kernels.hip", "capi.hip"]
 # The encode kernels keep MFMA accumulators in ordinary VGPRs (no AGPR
 # round trips between the phase tile and the sine/cosine that consume it).
-SOURCE_FLAGS = {"encode_kernels.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+SOURCE_FLAGS = {"encode_kernels.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+                "grad_kernels.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # Packed FP32 VALU ops are disabled for the device code (see the design notes).

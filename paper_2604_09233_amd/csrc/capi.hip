@@ -239,6 +239,7 @@ struct Layout {
   size_t o_sA, o_sB, o_vA, o_vB, o_tmax, o_dataE, o_dataH, o_epart, o_hpart, o_bmax, o_unscale, o_sensj, o_smax;
   size_t o_r, o_p, o_q, o_b, o_part, o_alpha, o_scal, o_hist, o_info, o_stop, o_V, o_rpart, o_rn;
   size_t o_PE, o_PH;  // resident P (NFS_OP_CG_RESIDENT)
+  GradShape grad;     // one-pass grad_kcoef (FP32), over everything from o_sA on
   size_t total;
 };
 
@@ -307,11 +308,11 @@ static Layout make_layout(const nfs_ctx* ctx, const nfs_problem* pr, int op, int
   // E^H streams samples (role A) against held voxels (role B)
   y.o_vA = needE ? take((size_t)y.LC * phase_chunk_bytes(y.NQ)) : 0;
   y.o_sB = needE ? take((size_t)y.KC * phase_chunk_bytes(y.NQ)) : 0;
-  y.o_sA = needH ? take((size_t)y.KC * phase_chunk_bytes(y.NQ)) : 0;
-  y.o_vB = needH ? take((size_t)y.LC * phase_chunk_bytes(y.NQ)) : 0;
   y.o_tmax = take(2 * kMaxTerms * 4);
   y.o_bmax = take(kBmaxBlocks * 4);
   y.o_unscale = take(2 * 4);
+  y.o_sA = needH ? take((size_t)y.KC * phase_chunk_bytes(y.NQ)) : 0;
+  y.o_vB = needH ? take((size_t)y.LC * phase_chunk_bytes(y.NQ)) : 0;
   y.o_dataE = needE ? take((size_t)y.LC * y.NB * data_chunk_bytes(prec)) : 0;
   y.o_dataH = needH ? take((size_t)y.KC * y.NB * data_chunk_bytes(prec)) : 0;
   if (cg) {
@@ -340,6 +341,10 @@ static Layout make_layout(const nfs_ctx* ctx, const nfs_problem* pr, int op, int
   // split partials last: their sizes depend on the encode shapes
   y.o_epart = needE ? take(epart_bytes(y.shE, y.NB)) : 0;
   y.o_hpart = needH ? take(hpart_bytes(y.shH)) : 0;
+  if (op == NFS_OP_EHE && prec == PREC_FP32 && y.P > 0) {
+    y.grad = grad_shape(y.K, y.L, y.G, y.P, ctx && ctx->n_cu > 0 ? ctx->n_cu : 256, o - y.o_sA);
+    o = std::max(o, y.o_sA + y.grad.total);  // larger only for a few chunks with over 16 terms
+  }
   y.total = o;
   return y;
 }
@@ -1859,7 +1864,12 @@ extern "C" int nfs_encode_backward(nfs_ctx* ctx, const nfs_problem* prob, const 
                            c.s),
             "grad_b0");
   }
-  if (grad_kcoef && y.K > 0 && y.P > 0) {
+  if (grad_kcoef && y.K > 0 && y.P > 0 && precision == NFS_FP32) {
+    NFS_TRY(launch_grad_kcoef_fused(y.grad, at<void>(ws, y.o_sB), at<void>(ws, y.o_vA), r, c.sens, prob->fields, G,
+                                    y.K, y.L, y.G, y.P, y.NQ, at<unsigned>(ws, y.o_tmax), at<float>(ws, y.o_bmax),
+                                    at<float>(ws, y.o_unscale), at<void>(ws, y.o_sA), grad_kcoef, c.s),
+            "grad_kcoef_fused");
+  } else if (grad_kcoef && y.K > 0 && y.P > 0) {
     for (int b = 0; b < y.P; ++b) {
       if ((rc = seq_E(c, r, prob->fields + (int64_t)b * y.L))) return rc;
       NFS_TRY(launch_grad_kcoef(at<float>(ws, y.o_epart), y.shE.nsplit, y.KC * 16, y.NB, unscale_slot(c, 0), G, y.K,

@@ -18,21 +18,9 @@
 // (real columns interleaved per coil: column 2c is re, 2c+1 is im).
 #include <algorithm>
 
-#include "nfs_internal.h"
+#include "fragment.h"
 
 namespace nfs {
-
-typedef _Float16 h8 __attribute__((ext_vector_type(8)));
-typedef __bf16 b8 __attribute__((ext_vector_type(8)));
-typedef b8 b8_t;
-typedef float f4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u4 __attribute__((ext_vector_type(4)));
-
-constexpr double kInv2Pi = 0.159154943091895335768883763372514362;
-
-__device__ __forceinline__ float2 cmul(float2 a, float2 b) {
-  return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
-}
 
 // ---------------------------------------------------------------------------
 // Phase coefficients, split into f16 parts, in MFMA fragment order.
@@ -60,18 +48,6 @@ __device__ __forceinline__ float2 cmul(float2 a, float2 b) {
 // Per lane (g = lane / 16, n = lane % 16): item 16 chunk + n, slots
 // 32 q + 8 g + e, e = 0..7, stored as one 16-byte vector
 // out[(chunk * NQ + q) * 64 + lane].
-
-// e_b of the balancing power for term b, from the term maxima (identical on
-// both sides and in every kernel that reads it)
-__device__ __forceinline__ int term_shift(const unsigned* __restrict__ tmax, int b) {
-  const float ma = __uint_as_float(tmax[b]) * (float)kInv2Pi;
-  const float mh = __uint_as_float(tmax[kMaxTerms + b]);
-  if (!(ma > 0.f) || !(mh > 0.f) || !isfinite(ma) || !isfinite(mh)) return 0;
-  int ea, eh;
-  frexpf(ma, &ea);
-  frexpf(mh, &eh);
-  return (ea - eh) / 2;
-}
 
 // largest |a_b| (samples, before the 1/2pi scaling) and |h_b| (voxels) per
 // term; kTmaxSampBlocks workgroups for the samples, then kTmaxVoxBlocks for
@@ -188,37 +164,6 @@ __global__ __launch_bounds__(256) void absmax_kernel(const float2* __restrict__ 
     __syncthreads();
   }
   if (threadIdx.x == 0) bmax[blockIdx.x] = red[0];
-}
-
-// One lane's 8 fragment values of (chunk ch, column block nb) in the layout
-// of precision PREC (see below).
-template <int PREC>
-__device__ __forceinline__ void store_fragment(const float (&vals)[8], void* __restrict__ out, int64_t ch, int nb,
-                                               int NB, int lane) {
-  if (PREC == PREC_FP32) {
-    h8 hi, lo;
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      hi[u] = (_Float16)vals[u];
-      lo[u] = (_Float16)(vals[u] - (float)hi[u]);
-    }
-    ((h8*)out)[((ch * NB + nb) * 2 + 0) * 64 + lane] = hi;
-    ((h8*)out)[((ch * NB + nb) * 2 + 1) * 64 + lane] = lo;
-  } else if (PREC == PREC_FP16) {
-    h8 h;
-#pragma unroll
-    for (int u = 0; u < 8; ++u) h[u] = (_Float16)vals[u];
-    ((h8*)out)[(ch * NB + nb) * 64 + lane] = h;
-  } else {
-    b8 hi, lo;
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      hi[u] = (__bf16)vals[u];
-      lo[u] = (__bf16)(vals[u] - (float)hi[u]);
-    }
-    ((b8*)out)[((ch * NB + nb) * 2 + 0) * 64 + lane] = hi;
-    ((b8*)out)[((ch * NB + nb) * 2 + 1) * 64 + lane] = lo;
-  }
 }
 
 // ---------------------------------------------------------------------------
@@ -473,8 +418,6 @@ struct Stream {
   }
 };
 
-typedef __attribute__((address_space(3))) void lds_void;
-
 // Wave `wave` copies blocks wave, wave + 4, ... of chunk ch into `dst`
 // (global -> LDS directly, 16 bytes per lane, no registers involved).
 template <int PREC, int NB, int NQ>
@@ -496,17 +439,6 @@ template <int PREC>
 struct TileOperand {
   u4 hi, lo;  // lo used by the FP32 form only
 };
-
-// Phase tile on the f16 matrix cores: NQ chained 16x16x32 products.
-template <int NQ>
-__device__ __forceinline__ f4 phase_tile(const u4 (&ph)[NQ], const u4 (&hc)[NQ]) {
-  f4 p = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int q = 0; q < NQ; ++q)
-    p = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8, ph[q]), __builtin_bit_cast(h8, hc[q]), p, 0,
-                                               0, 0);
-  return p;
-}
 
 // sin/cos of a phase tile (revolutions; v_fract first when FRACT) and its
 // conversion to the contraction operand.
@@ -719,11 +651,7 @@ __device__ __forceinline__ void encode_block(const u4* __restrict__ heldcoef, co
   const int wave = threadIdx.x >> 6;
   const int64_t tile0 = (bx * kWaves + wave) * MT;
 
-  // bound on |phi| in revolutions: sum over terms of max|a_b| max|h_b|
-  float bound = 0.f;
-  if (lane < T) bound = __uint_as_float(tmax[lane]) * (float)kInv2Pi * __uint_as_float(tmax[kMaxTerms + lane]);
-  for (int off = 32; off > 0; off >>= 1) bound += __shfl_xor(bound, off);
-  const bool raw = bound < kRawPhaseBound;  // also false for NaN
+  const bool raw = raw_phase(tmax, T, lane);
 
   u4 hc[MT][NQ];
 #pragma unroll
@@ -753,14 +681,6 @@ __device__ __forceinline__ void encode_block(const u4* __restrict__ heldcoef, co
     stream_range<PREC, NQ, NB, MT, true>(strmcoef, sd, c0, c1, hc, acc, st0, st1, wave, lane);
 
   write_partials<OP, NB, MT>(acc, tile0, split, HC, out_part, sens, L, G, lane);
-}
-
-// XCD-aware order: block b of nblk goes to XCD b % 8 (round-robin dispatch);
-// renumbering makes each XCD take a contiguous range of blocks, which share
-// streamed chunks in that XCD's L2.
-__device__ __forceinline__ int64_t xcd_order(int64_t b, int64_t nblk) {
-  const int64_t per = nblk / 8;
-  return b < per * 8 ? (b % 8) * per + b / 8 : b;
 }
 
 template <int OP, int PREC, int NQ, int NB, int MT>
@@ -821,10 +741,7 @@ __global__ __launch_bounds__(256) void build_P_kernel(const u4* __restrict__ hel
                                                       int64_t HC, int64_t SC, const unsigned* __restrict__ tmax,
                                                       int T, h8* __restrict__ P) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  float bound = 0.f;
-  if (lane < T) bound = __uint_as_float(tmax[lane]) * (float)kInv2Pi * __uint_as_float(tmax[kMaxTerms + lane]);
-  for (int off = 32; off > 0; off >>= 1) bound += __shfl_xor(bound, off);
-  const bool raw = bound < kRawPhaseBound;
+  const bool raw = raw_phase(tmax, T, lane);
   const int64_t npair = HC * SC;
   for (int64_t pair = (int64_t)blockIdx.x * kWaves + wave; pair < npair; pair += (int64_t)gridDim.x * kWaves) {
     const int64_t ht = pair / SC, ch = pair - ht * SC;

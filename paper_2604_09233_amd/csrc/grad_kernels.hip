@@ -1,0 +1,354 @@
+// Gradient of the field coefficients in one pass (FP32 form).
+//
+// grad_kcoef[k][b] = Im sum_c G_c(k) conj((E (h_b o rho))_c(k)) needs E of P
+// different images when the sum over coils is taken last.  Taking it first
+// leaves one image-sized quantity per (sample, voxel) pair:
+//   grad_kcoef[k][b] = sum_l h_b(l) w(k, l),
+//   w(k, l) = Im(exp(-i phi(k, l)) D(k, l)),  D(k, l) = sum_c conj(S_c(l) rho(l)) G_c(k),
+// so every pair is visited once: the phase tile and its sine and cosine as in
+// the encode kernel, D as a contraction over the coils whose result has the
+// phase tile's layout (streamed voxels x held samples), w on the VALU, and w
+// (which is then the A operand of a product over voxels, in place) against
+// the field values of 16 terms per column block.  All three products take
+// two-part f16 operands, three matrix-core products each, like the FP32 form
+// of the encode kernel; per 16 x 16 tile that is NQ + 6 NK + 1.5 NP
+// matrix-core instructions and 8 transcendentals in place of P times the
+// FP32 encode tile's NQ + 3 NB and 8.
+#include <algorithm>
+
+#include "fragment.h"
+
+namespace nfs {
+
+// Operand layouts (per lane g = lane / 16, n = lane % 16, slots e = 0..7,
+// 16-byte vectors; part 0 = hi, 1 = lo; "kk" blocks of 16 coils):
+//  voxels   q  [(chunk * NK + kk) * 2 + part][64]: voxel 16 chunk + n, coil
+//           16 kk + 4 g + e / 2, re / im of S_c rho (e % 2), scaled;
+//  samples  Gf [(tile * NK + kk) * 2 + part][64]: sample 16 tile + n, same
+//           coils, (Gr, Gi), scaled per sample: the operand of Re D; that of
+//           Im D, (Gi, -Gr), is the same words with their halves turned;
+//  fields   hf [(pair * NP + np) * 2 + part][64]: term 16 np + n, voxel
+//           32 pair + 16 (e / 4) + 4 g + e % 4, scaled per term.
+// The scales are powers of two: |q| < 2^8 / (4 G) and |G| < 2^8 keep |w|
+// below 2^14 (|D| <= 2 G max|q| max|G|, |w| <= sqrt(2) |D|), |h| < 2.
+__device__ __forceinline__ void store_split(const float (&v)[8], h8* out, int64_t block, int lane) {
+  h8 hi, lo;
+  split8(v, hi, lo);
+  out[(block * 2 + 0) * 64 + lane] = hi;
+  out[(block * 2 + 1) * 64 + lane] = lo;
+}
+
+__device__ __forceinline__ float pow2_below(float mx, int top) {  // largest 2^s with mx 2^s < 2^top
+  if (!(mx > 0.f) || !isfinite(mx)) return 1.f;
+  int e;
+  frexpf(mx, &e);
+  const int s = top - e;
+  return ldexpf(1.f, s > 100 ? 100 : (s < -100 ? -100 : s));
+}
+
+__global__ __launch_bounds__(256) void grad_pack_q_kernel(const float2* __restrict__ rho,
+                                                          const float2* __restrict__ sens, int64_t L, int G, int NK,
+                                                          int64_t LC, const float* __restrict__ bmax, int top,
+                                                          float* __restrict__ unscale, h8* __restrict__ out) {
+  __shared__ float red[kBmaxBlocks];
+  red[threadIdx.x] = bmax[threadIdx.x];
+  __syncthreads();
+  for (int w = kBmaxBlocks / 2; w > 0; w >>= 1) {
+    if ((int)threadIdx.x < w) red[threadIdx.x] = fmaxf(red[threadIdx.x], red[threadIdx.x + w]);
+    __syncthreads();
+  }
+  const float scale = pow2_below(red[0], top);
+  if (blockIdx.x == 0 && threadIdx.x == 0) *unscale = 1.f / scale;
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= LC * NK * 64) return;
+  const int lane = (int)(i & 63), g = lane >> 4;
+  const int64_t blk = i >> 6, l = blk / NK * kChunk + (lane & 15);
+  const int kk = (int)(blk % NK);
+  float v[8];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int c = kk * 16 + g * 4 + j;
+    float2 q = make_float2(0.f, 0.f);
+    if (l < L && c < G) q = cmul(sens[(int64_t)c * L + l], rho[l]);
+    v[2 * j] = q.x * scale;
+    v[2 * j + 1] = q.y * scale;
+  }
+  store_split(v, out, blk, lane);
+}
+
+__global__ __launch_bounds__(256) void grad_pack_G_kernel(const float2* __restrict__ gm, int64_t K, int G, int NK,
+                                                          int64_t KC, float* __restrict__ gunscale,
+                                                          h8* __restrict__ out) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= KC * NK * 64) return;
+  const int lane = (int)(i & 63), g = lane >> 4;
+  const int64_t blk = i >> 6, k = blk / NK * kChunk + (lane & 15);
+  const int kk = (int)(blk % NK);
+  float mx = 0.f;
+  if (k < K)
+    for (int c = 0; c < G; ++c) {
+      const float2 a = gm[(int64_t)c * K + k];
+      mx = fmaxf(mx, fmaxf(fabsf(a.x), fabsf(a.y)));
+    }
+  const float scale = pow2_below(mx, 8);
+  if (kk == 0 && g == 0) gunscale[k] = 1.f / scale;  // KC * 16 entries
+  float re[8];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int c = kk * 16 + g * 4 + j;
+    float2 a = make_float2(0.f, 0.f);
+    if (k < K && c < G) a = gm[(int64_t)c * K + k];
+    re[2 * j] = a.x * scale;
+    re[2 * j + 1] = a.y * scale;
+  }
+  store_split(re, out, blk, lane);
+}
+
+// 2^-e_b with max|h_b| 2^-e_b in [1, 2)
+__device__ __forceinline__ float field_scale(const unsigned* tmax, int b) {
+  return pow2_below(__uint_as_float(tmax[kMaxTerms + b]), 1);
+}
+
+__global__ __launch_bounds__(256) void grad_pack_h_kernel(const float* __restrict__ fields, int64_t L, int P, int NP,
+                                                          int64_t npair, const unsigned* __restrict__ tmax,
+                                                          h8* __restrict__ out) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= npair * NP * 64) return;
+  const int lane = (int)(i & 63), g = lane >> 4;
+  const int64_t blk = i >> 6, pair = blk / NP;
+  const int b = (int)(blk % NP) * 16 + (lane & 15);
+  float v[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const int64_t l = pair * 32 + (e >> 2) * 16 + g * 4 + (e & 3);
+    v[e] = b < P && l < L ? fields[(int64_t)b * L + l] * field_scale(tmax, b + 1) : 0.f;
+  }
+  store_split(v, out, blk, lane);
+}
+
+// Grid (ceil(HC / (kWaves MT)), nsplit), held samples x streamed pairs of
+// voxel chunks, staged through LDS and remapped to XCDs as in encode_kernel.
+template <int NQ, int NK, int NP, int MT, bool FRACT>
+__device__ __forceinline__ void grad_stream(const u4* __restrict__ strmcoef, const u4* __restrict__ q,
+                                            const u4* __restrict__ hf, int64_t p0, int64_t p1, int64_t LC,
+                                            const u4 (&hc)[MT][NQ], const u4 (&gb)[MT][NK][2][2], f4 (&acc)[MT][NP],
+                                            u4 (*stage)[(2 * NQ + 4 * NK + 2 * NP) * 64], int wave, int lane) {
+  constexpr int kPh = 2 * NQ, kQ = 4 * NK, kBlk = kPh + kQ + 2 * NP;
+  // a pair's blocks: phase parts of both chunks, q of both, field values; the
+  // second chunk of the last pair may not exist and repeats the first (its
+  // field values are zero)
+  auto load = [&](int64_t pair, u4* dst) {
+#pragma unroll
+    for (int blk = wave; blk < kBlk; blk += kWaves) {
+      const u4* src;
+      if (blk < kPh) {
+        const int64_t ch = 2 * pair + blk / NQ;
+        src = strmcoef + ((ch < LC ? ch : LC - 1) * NQ + blk % NQ) * 64;
+      } else if (blk < kPh + kQ) {
+        const int64_t ch = 2 * pair + (blk - kPh) / (2 * NK);
+        src = q + ((ch < LC ? ch : LC - 1) * (2 * NK) + (blk - kPh) % (2 * NK)) * 64;
+      } else {
+        src = hf + (pair * (2 * NP) + (blk - kPh - kQ)) * 64;
+      }
+      __builtin_amdgcn_global_load_lds((const void*)(src + lane), (lds_void*)(dst + blk * 64), 16, 0, 0);
+    }
+  };
+  auto h = [](u4 v) { return __builtin_bit_cast(h8, v); };
+  if (p0 < p1) load(p0, stage[0]);
+  int buf = 0;
+  for (int64_t pair = p0; pair < p1; ++pair) {
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (pair + 1 < p1) load(pair + 1, stage[buf ^ 1]);
+    const u4* st = stage[buf];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+      float w[8];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        u4 ph[NQ];
+#pragma unroll
+        for (int i = 0; i < NQ; ++i) ph[i] = st[(u * NQ + i) * 64 + lane];
+        const f4 p = phase_tile<NQ>(ph, hc[mt]);
+        f4 dr = {0.f, 0.f, 0.f, 0.f}, di = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kk = 0; kk < NK; ++kk) {
+          const h8 qh = h(st[(kPh + (u * NK + kk) * 2) * 64 + lane]), ql = h(st[(kPh + (u * NK + kk) * 2 + 1) * 64 + lane]);
+          dr = __builtin_amdgcn_mfma_f32_16x16x32_f16(ql, h(gb[mt][kk][0][0]), dr, 0, 0, 0);
+          di = __builtin_amdgcn_mfma_f32_16x16x32_f16(ql, h(gb[mt][kk][1][0]), di, 0, 0, 0);
+          dr = __builtin_amdgcn_mfma_f32_16x16x32_f16(qh, h(gb[mt][kk][0][1]), dr, 0, 0, 0);
+          di = __builtin_amdgcn_mfma_f32_16x16x32_f16(qh, h(gb[mt][kk][1][1]), di, 0, 0, 0);
+          dr = __builtin_amdgcn_mfma_f32_16x16x32_f16(qh, h(gb[mt][kk][0][0]), dr, 0, 0, 0);
+          di = __builtin_amdgcn_mfma_f32_16x16x32_f16(qh, h(gb[mt][kk][1][0]), di, 0, 0, 0);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float x = FRACT ? __builtin_amdgcn_fractf(p[r]) : p[r];
+          w[4 * u + r] = __builtin_amdgcn_cosf(x) * di[r] - __builtin_amdgcn_sinf(x) * dr[r];
+        }
+      }
+      h8 wh, wl;
+      split8(w, wh, wl);
+#pragma unroll
+      for (int np = 0; np < NP; ++np) {
+        const h8 fh = h(st[(kPh + kQ + 2 * np) * 64 + lane]), fl = h(st[(kPh + kQ + 2 * np + 1) * 64 + lane]);
+        f4 t = {0.f, 0.f, 0.f, 0.f};
+        t = __builtin_amdgcn_mfma_f32_16x16x32_f16(wl, fh, t, 0, 0, 0);
+        t = __builtin_amdgcn_mfma_f32_16x16x32_f16(wh, fl, t, 0, 0, 0);
+        t = __builtin_amdgcn_mfma_f32_16x16x32_f16(wh, fh, t, 0, 0, 0);
+        acc[mt][np] += t;
+      }
+    }
+    buf ^= 1;
+  }
+}
+
+template <int NQ, int NK, int NP, int MT>
+__global__ __launch_bounds__(256) void grad_kcoef_fused_kernel(const u4* __restrict__ heldcoef,
+                                                               const u4* __restrict__ strmcoef,
+                                                               const u4* __restrict__ q, const u4* __restrict__ gf,
+                                                               const u4* __restrict__ hf, int64_t HC, int64_t LC,
+                                                               int64_t npair, int64_t pps, float* __restrict__ part,
+                                                               const unsigned* __restrict__ tmax, int T) {
+  __shared__ u4 stage[2][(2 * NQ + 4 * NK + 2 * NP) * 64];
+  const int64_t b = xcd_order(blockIdx.x + (int64_t)gridDim.x * blockIdx.y, (int64_t)gridDim.x * gridDim.y);
+  const int64_t bx = b % gridDim.x, split = b / gridDim.x;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t tile0 = (bx * kWaves + wave) * MT;
+  const bool raw = raw_phase(tmax, T, lane);
+  u4 hc[MT][NQ], gb[MT][NK][2][2];
+  f4 acc[MT][NP];
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) {
+    const int64_t tile = tile0 + mt < HC ? tile0 + mt : HC - 1;  // past the end: not written
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) hc[mt][i] = heldcoef[(tile * NQ + i) * 64 + lane];
+#pragma unroll
+    for (int kk = 0; kk < NK; ++kk)
+#pragma unroll
+      for (int part = 0; part < 2; ++part) {
+        const u4 v = gf[((tile * NK + kk) * 2 + part) * 64 + lane];
+        gb[mt][kk][0][part] = v;
+        gb[mt][kk][1][part] = ((v >> 16) | (v << 16)) ^ 0x80000000u;
+      }
+#pragma unroll
+    for (int np = 0; np < NP; ++np) acc[mt][np] = f4{0.f, 0.f, 0.f, 0.f};
+  }
+  const int64_t p0 = split * pps, p1 = p0 + pps < npair ? p0 + pps : npair;
+  if (raw) grad_stream<NQ, NK, NP, MT, false>(strmcoef, q, hf, p0, p1, LC, hc, gb, acc, stage, wave, lane);
+  else grad_stream<NQ, NK, NP, MT, true>(strmcoef, q, hf, p0, p1, LC, hc, gb, acc, stage, wave, lane);
+  const int g = lane >> 4, n = lane & 15;
+  float* o = part + (size_t)split * (size_t)HC * 16 * (NP * 16);
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) {
+    if (tile0 + mt >= HC) continue;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int np = 0; np < NP; ++np)
+        o[((tile0 + mt) * 16 + g * 4 + r) * (NP * 16) + np * 16 + n] = acc[mt][np][r];
+  }
+}
+
+// out[k][b] = the split sums, unscaled
+__global__ __launch_bounds__(256) void grad_kcoef_finish_kernel(const float* __restrict__ part, int nsplit,
+                                                                int64_t HC16, int NP, const float* __restrict__ unscale,
+                                                                const float* __restrict__ gunscale,
+                                                                const unsigned* __restrict__ tmax, int64_t K, int P,
+                                                                float* __restrict__ out) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= K * P) return;
+  const int64_t k = i / P;
+  const int b = (int)(i - k * P), ncol = NP * 16;
+  float v = 0.f;
+  for (int s = 0; s < nsplit; ++s) v += part[((size_t)s * HC16 + k) * ncol + b];
+  out[i] = v / field_scale(tmax, b + 1) * *unscale * gunscale[k];
+}
+
+// ---------------------------------------------------------------------------
+static int grad_nk(int G) { return G <= 16 ? 1 : G <= 32 ? 2 : 4; }
+static int grad_np(int P) { return P <= 16 ? 1 : 2; }
+// held tiles per wave: the samples' operands take 16 NK registers a tile
+static int grad_mt(int G) { return grad_nk(G) <= 2 ? 2 : 1; }
+
+GradShape grad_shape(int64_t K, int64_t L, int G, int P, int n_cu, size_t avail) {
+  GradShape g{};
+  const int64_t KC = cdiv(K, kChunk), LC = cdiv(L, kChunk);
+  g.NK = grad_nk(G);
+  g.NP = grad_np(P);
+  g.npair = cdiv(LC, 2);
+  auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
+  g.o_q = 0;
+  g.o_G = g.o_q + al((size_t)LC * g.NK * 2 * 1024);
+  g.o_h = g.o_G + al((size_t)KC * g.NK * 2 * 1024);
+  g.o_gs = g.o_h + al((size_t)g.npair * g.NP * 2 * 1024);
+  g.o_part = g.o_gs + al((size_t)KC * kChunk * 4);
+  const size_t one = (size_t)KC * kChunk * g.NP * 16 * 4;  // a multiple of 256
+  // about four workgroups per CU, at least 8 pairs each, inside the space the
+  // E^H E workspace has anyway
+  const int64_t gx = cdiv(KC, (int64_t)kWaves * grad_mt(G));
+  const int64_t fit = avail > g.o_part && one ? (int64_t)((avail - g.o_part) / one) : 1;
+  int64_t ns = gx > 0 ? cdiv((int64_t)4 * n_cu, gx) : 1;
+  ns = std::max<int64_t>(1, std::min<int64_t>({ns, g.npair / 8, 64, fit}));
+  g.pps = cdiv(g.npair, ns);
+  g.nsplit = (int)std::max<int64_t>(1, g.pps > 0 ? cdiv(g.npair, g.pps) : 1);
+  g.total = g.o_part + g.nsplit * one;
+  return g;
+}
+
+template <int NQ>
+static hipError_t launch_fused_nq(const GradShape& g, int G, const u4* held, const u4* strm, const char* ws, int64_t KC,
+                                  int64_t LC, float* part, const unsigned* tmax, int T, hipStream_t s) {
+  const dim3 gr((unsigned)cdiv(KC, (int64_t)kWaves * grad_mt(G)), (unsigned)g.nsplit), bl(64 * kWaves);
+  const u4 *q = (const u4*)(ws + g.o_q), *gf = (const u4*)(ws + g.o_G), *hf = (const u4*)(ws + g.o_h);
+  switch (g.NK * 4 + g.NP) {
+#define NFS_GRAD(nk, np, mt)                                                                                       \
+  case nk * 4 + np:                                                                                                \
+    hipLaunchKernelGGL((grad_kcoef_fused_kernel<NQ, nk, np, mt>), gr, bl, 0, s, held, strm, q, gf, hf, KC, LC, g.npair, \
+                       g.pps, part, tmax, T);                                                                       \
+    break;
+    NFS_GRAD(1, 1, 2)
+    NFS_GRAD(1, 2, 2)
+    NFS_GRAD(2, 1, 2)
+    NFS_GRAD(2, 2, 2)
+    NFS_GRAD(4, 1, 1)
+    NFS_GRAD(4, 2, 1)
+#undef NFS_GRAD
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_grad_kcoef_fused(const GradShape& g, const void* heldcoef, const void* strmcoef, const float2* rho,
+                                   const float2* sens, const float* fields, const float2* grad_m, int64_t K, int64_t L,
+                                   int G, int P, int NQ, const unsigned* tmax, float* bmax, float* unscale, void* ws,
+                                   float* out, hipStream_t s) {
+  if (K == 0 || P == 0) return hipSuccess;
+  if (L == 0) return launch_fill_zero(out, K * P, s);
+  const int64_t KC = cdiv(K, kChunk), LC = cdiv(L, kChunk);
+  char* w = (char*)ws;
+  hipError_t e = launch_absmax(rho, sens, nullptr, L, 1, 0, G, bmax, nullptr, s);
+  if (e != hipSuccess) return e;
+  int lg = 0;
+  while ((1 << lg) < 4 * G) ++lg;
+  auto blocks = [](int64_t n) { return dim3((unsigned)cdiv(n, 256)); };
+  hipLaunchKernelGGL(grad_pack_q_kernel, blocks(LC * g.NK * 64), dim3(256), 0, s, rho, sens, L, G, g.NK, LC, bmax,
+                     14 - 8 - lg + 2, unscale, (h8*)(w + g.o_q));
+  hipLaunchKernelGGL(grad_pack_G_kernel, blocks(KC * g.NK * 64), dim3(256), 0, s, grad_m, K, G, g.NK, KC,
+                     (float*)(w + g.o_gs), (h8*)(w + g.o_G));
+  hipLaunchKernelGGL(grad_pack_h_kernel, blocks(g.npair * g.NP * 64), dim3(256), 0, s, fields, L, P, g.NP, g.npair,
+                     tmax, (h8*)(w + g.o_h));
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  float* part = (float*)(w + g.o_part);
+  const u4 *held = (const u4*)heldcoef, *strm = (const u4*)strmcoef;
+  e = NQ == 1   ? launch_fused_nq<1>(g, G, held, strm, w, KC, LC, part, tmax, P + 1, s)
+      : NQ == 2 ? launch_fused_nq<2>(g, G, held, strm, w, KC, LC, part, tmax, P + 1, s)
+      : NQ == 3 ? launch_fused_nq<3>(g, G, held, strm, w, KC, LC, part, tmax, P + 1, s)
+                : hipErrorInvalidValue;
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(grad_kcoef_finish_kernel, blocks(K * P), dim3(256), 0, s, part, g.nsplit, KC * kChunk, g.NP,
+                     unscale, (const float*)(w + g.o_gs), tmax, K, P, out);
+  return hipGetLastError();
+}
+
+}  // namespace nfs

@@ -177,6 +177,24 @@ hipError_t launch_grad_b0(const float2* hpart, int nsplit, int64_t HC16, int64_t
 hipError_t launch_grad_kcoef(const float* epart, int nsplit, int64_t HC16, int NB, const float* unscale,
                              const float2* grad_m, int64_t K, int G, int P, int b, float* out, hipStream_t s);
 
+// ---- gradient of the field coefficients (grad_kernels.hip) --------------------
+// Layout and shape of the one-pass form: blocks of 16 coils and of 16 terms,
+// pairs of voxel chunks (per split), and byte offsets of its operands and
+// partials in a buffer of `total` bytes.
+struct GradShape {
+  int NK, NP, nsplit;
+  int64_t npair, pps;
+  size_t o_q, o_G, o_h, o_gs, o_part, total;
+};
+// as many splits as fit into `avail` bytes (at least one)
+GradShape grad_shape(int64_t K, int64_t L, int G, int P, int n_cu, size_t avail);
+// grad_kcoef [K][P] (FP32 form); heldcoef, strmcoef: phase parts of the
+// samples (role B) and voxels (role A); ws: grad_shape().total bytes
+hipError_t launch_grad_kcoef_fused(const GradShape& g, const void* heldcoef, const void* strmcoef, const float2* rho,
+                                   const float2* sens, const float* fields, const float2* grad_m, int64_t K, int64_t L,
+                                   int G, int P, int NQ, const unsigned* tmax, float* bmax, float* unscale, void* ws,
+                                   float* out, hipStream_t s);
+
 // ---- stopping-criteria instrumentation (quality_kernels.hip) ------------------
 // mean SSIM of |imgs[i]| against |ref| for i < n_img into out[i] (float64);
 // images [n_img][L] complex, L = nx ny nz (x fastest); needs nx, ny >= 11 and
