@@ -246,8 +246,13 @@ struct Layout {
 static size_t epart_bytes(const EncodeShape& sh, int NB) { return (size_t)sh.nsplit * sh.HC * 16 * NB * 16 * 4; }
 static size_t hpart_bytes(const EncodeShape& sh) { return (size_t)sh.nsplit * sh.HC * 16 * 8; }
 
-static int choose_split(int64_t held_chunks, int64_t strm_chunks, int MT, int n_cu) {
-  const int64_t gx = cdiv(held_chunks, (int64_t)kWaves * MT);
+// Default split count of the solves: about four workgroups per CU at the held
+// tiles `MT`, at least 32 streamed chunks each.  The split count is part of
+// a solve's arithmetic (the order of the split sums), so it stays what it was
+// when the held tiles of four column blocks went from two to four; iterates
+// are reproduced bit for bit.
+static int solve_split(int64_t held_chunks, int64_t strm_chunks, int NB, int n_cu) {
+  const int64_t gx = cdiv(held_chunks, (int64_t)kWaves * (NB <= 2 ? 4 : 2));
   if (gx <= 0) return 1;
   int64_t ns = cdiv(4LL * n_cu, gx);
   const int64_t maxs = strm_chunks / 32 > 1 ? strm_chunks / 32 : 1;
@@ -257,13 +262,36 @@ static int choose_split(int64_t held_chunks, int64_t strm_chunks, int MT, int n_
   return (int)ns;
 }
 
+// Default split count of single operators (E, E^H, E^H E, backward): more
+// workgroups than the resident ones even out their uneven ends, so E aims at
+// 13 per CU (at least 32 chunks each) and E^H, whose workgroups end in the
+// coil sums, at 8 (at least 64 chunks), never below the solves' count.
+// Measured (fp16 / fp32, us, solves' count -> this): 200x200, 16 coils, 90 000
+// samples E 1008 -> 822 / 1997 -> 1640, E^H 895 -> 865; 48x48x24, 32 coils,
+// 32 000 samples E 648 -> 554 / 1375 -> 1255, E^H 731 -> 596; 128x128, 16
+// coils, 60 000 samples E 265 -> 237, E^H 247 -> 244.  Where even that leaves
+// CUs idle, a call of one direction (`alone`) goes down to 8 chunks a split,
+// as long as E's partials stay small (32x32, 2048 samples: E call 43 -> 37).
+static int operator_split(int op, int64_t held_chunks, int64_t strm_chunks, int NB, int MT, int n_cu, bool alone) {
+  const int base = solve_split(held_chunks, strm_chunks, NB, n_cu);
+  const int64_t gx = cdiv(held_chunks, (int64_t)kWaves * MT);
+  if (gx <= 0) return base;
+  int64_t ns = std::min(cdiv((op == OP_E ? 13LL : 8LL) * n_cu, gx), strm_chunks / (op == OP_E ? 32 : 64));
+  ns = std::max<int64_t>(ns, base);
+  if (alone && gx * ns < n_cu) {
+    const int64_t room = op == OP_E ? (512 << 10) / (held_chunks * kChunk * NB * 16 * 4) : 64;
+    ns = std::max(ns, std::min({cdiv(n_cu, gx), strm_chunks / 8, room}));
+  }
+  return (int)std::min<int64_t>(ns, 64);
+}
+
 // Encode shape of one direction: held-tile count MT and split count, from
 // (in order) an explicit override, the context's autotuned entry, or the
-// default heuristic.
+// defaults for the call `call` (an nfs_op).  Held tiles do not change results.
 static EncodeShape encode_shape(const nfs_ctx* ctx, const nfs_problem* pr, int op, int prec, int NQ, int NB,
-                                int64_t HC, int64_t SC, const int* ov) {
+                                int64_t HC, int64_t SC, const int* ov, int call = NFS_OP_CG) {
   const int n_cu = ctx ? ctx->n_cu : 256;
-  int MT = held_tiles(NB), ns = 0;
+  int MT = 0, ns = 0;
   if (ov) {
     MT = ov[0];
     ns = ov[1];
@@ -274,15 +302,21 @@ static EncodeShape encode_shape(const nfs_ctx* ctx, const nfs_problem* pr, int o
       ns = it->second.second;
     }
   }
-  if (ns < 1) ns = choose_split(HC, SC, MT, n_cu);
+  if (ns < 1) {
+    const int big = valid_held_tiles(NB, 4) ? 4 : 2;
+    const bool solve = call == NFS_OP_CG || call == NFS_OP_CG_RESIDENT;
+    ns = solve ? solve_split(HC, SC, NB, n_cu) : operator_split(op, HC, SC, NB, big, n_cu, call != NFS_OP_EHE);
+    // four held tiles read each staged chunk half as often as two, which
+    // pays once two workgroups per CU are left (48x48x24, 32 coils: E 648 ->
+    // 590 us; 64x64, 8 coils, 12 000 samples, 1.5 per CU: two are 10 % faster)
+    MT = cdiv(HC, (int64_t)kWaves * big) * ns >= 2 * n_cu ? big : 2;
+  }
   EncodeShape sh{op, prec, NQ, NB, MT, HC, SC, ns, 0};
   sh.cps = cdiv(SC, ns > 0 ? ns : 1);
   return sh;
 }
 
-// ovE / ovH: optional {MT, nsplit} overrides of the E / E^H shapes (tuning)
-static Layout make_layout(const nfs_ctx* ctx, const nfs_problem* pr, int op, int prec, int n_iter, int reorth,
-                          const int* ovE = nullptr, const int* ovH = nullptr) {
+static Layout make_layout(const nfs_ctx* ctx, const nfs_problem* pr, int op, int prec, int n_iter, int reorth) {
   Layout y{};
   y.L = pr->n_vox;
   y.K = pr->n_samp;
@@ -293,10 +327,10 @@ static Layout make_layout(const nfs_ctx* ctx, const nfs_problem* pr, int op, int
   y.NQ = phase_instrs(y.P);
   y.NB = col_blocks(y.G);
   y.prec = prec;
-  y.shE = encode_shape(ctx, pr, OP_E, prec, y.NQ, y.NB, y.KC, y.LC, ovE);
-  y.shH = encode_shape(ctx, pr, OP_EH, prec, y.NQ, y.NB, y.LC, y.KC, ovH);
-  const bool needE = op != NFS_OP_EH, needH = op != NFS_OP_E;
   const bool cg = op == NFS_OP_CG || op == NFS_OP_CG_RESIDENT;
+  y.shE = encode_shape(ctx, pr, OP_E, prec, y.NQ, y.NB, y.KC, y.LC, nullptr, op);
+  y.shH = encode_shape(ctx, pr, OP_EH, prec, y.NQ, y.NB, y.LC, y.KC, nullptr, op);
+  const bool needE = op != NFS_OP_EH, needH = op != NFS_OP_E;
 
   size_t o = 0;
   auto take = [&](size_t bytes) {
@@ -342,7 +376,7 @@ static Layout make_layout(const nfs_ctx* ctx, const nfs_problem* pr, int op, int
   y.o_epart = needE ? take(epart_bytes(y.shE, y.NB)) : 0;
   y.o_hpart = needH ? take(hpart_bytes(y.shH)) : 0;
   if (op == NFS_OP_EHE && prec == PREC_FP32 && y.P > 0) {
-    y.grad = grad_shape(y.K, y.L, y.G, y.P, ctx && ctx->n_cu > 0 ? ctx->n_cu : 256, o - y.o_sA);
+    y.grad = grad_shape(y.K, y.L, y.G, y.P, ctx ? ctx->n_cu : 256, o - y.o_sA);
     o = std::max(o, y.o_sA + y.grad.total);  // larger only for a few chunks with over 16 terms
   }
   y.total = o;
@@ -2224,7 +2258,7 @@ extern "C" int nfs_tuned_shape(const nfs_ctx* ctx, const nfs_problem* prob, int 
   if (rc) return rc;
   if ((rc = check_prec(precision, fn))) return rc;
   if (op != NFS_OP_E && op != NFS_OP_EH) return fail(NFS_EINVAL, "%s: op must be NFS_OP_E or NFS_OP_EH", fn);
-  const Layout y = make_layout(ctx, prob, NFS_OP_EHE, precision, 0, 0);
+  const Layout y = make_layout(ctx, prob, NFS_OP_CG, precision, 0, 0);
   const EncodeShape& sh = op == NFS_OP_E ? y.shE : y.shH;
   *held_tiles_out = sh.MT;
   *nsplit_out = sh.nsplit;

@@ -880,20 +880,37 @@ __global__ void grad_b0_kernel(const float2* __restrict__ hpart, int nsplit, int
   out[l] = (r.x * v.y - r.y * v.x) * u;
 }
 
-// grad_kcoef[k][b] = Im(sum_c G[c][k] conj(Z[k][c])), Z = E (h_b o rho) as E partials
-__global__ void grad_kcoef_kernel(const float* __restrict__ epart, int nsplit, int64_t HC16, int NB,
-                                  const float* __restrict__ unscale, const float2* __restrict__ grad_m, int64_t K,
-                                  int G, int P, int b, float* __restrict__ out) {
-  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= K) return;
-  const int ncol = NB * 16;
-  float acc = 0.f;
-  for (int c = 0; c < G; ++c) {
-    const float2 z = sum_strided((const float2*)(epart + k * ncol + 2 * c), nsplit, HC16 * ncol / 2);
-    const float2 g = grad_m[(int64_t)c * K + k];
-    acc += g.y * z.x - g.x * z.y;
+// grad_kcoef[k][b] = Im(sum_c G[c][k] conj(Z[k][c])), Z = E (h_b o rho) as E
+// partials.  `rows` samples per workgroup: their partial rows and G are read
+// as they lie, the products meet in LDS and one thread per sample adds its
+// coils in order (a sample per lane, reading 8 of every 128 bytes, took
+// longer than the E before it).
+__global__ __launch_bounds__(256) void grad_kcoef_kernel(const float* __restrict__ epart, int nsplit, int64_t HC16,
+                                                         int NB, const float* __restrict__ unscale,
+                                                         const float2* __restrict__ grad_m, int64_t K, int G, int P,
+                                                         int b, int rows, float* __restrict__ out) {
+  __shared__ float2 tile[64][kFinishRows + 1];
+  const int64_t k0 = (int64_t)blockIdx.x * rows;
+  const int nc = NB * 8;
+  for (int i = threadIdx.x; i < rows * nc; i += 256) {
+    const int r = i / nc, c = i - r * nc;
+    if (c >= G || k0 + r >= K) continue;
+    tile[c][r] = sum_strided((const float2*)epart + (k0 + r) * nc + c, nsplit, HC16 * nc);
   }
-  out[k * P + b] = acc * (unscale ? *unscale : 1.f);
+  __syncthreads();
+  for (int i = threadIdx.x; i < rows * G; i += 256) {
+    const int c = i / rows, r = i - c * rows;
+    if (k0 + r >= K) continue;
+    const float2 g = grad_m[(int64_t)c * K + k0 + r], z = tile[c][r];
+    tile[c][r].x = g.y * z.x - g.x * z.y;
+  }
+  __syncthreads();
+  const int r = threadIdx.x;
+  if (r < rows && k0 + r < K) {
+    float acc = 0.f;
+    for (int c = 0; c < G; ++c) acc += tile[c][r].x;
+    out[(k0 + r) * P + b] = acc * (unscale ? *unscale : 1.f);
+  }
 }
 
 __global__ void fill_zero_kernel(float* __restrict__ p, int64_t n) {
@@ -909,6 +926,9 @@ __global__ void fill_kernel(float* __restrict__ p, int64_t n, float v) {
 // ---------------------------------------------------------------------------
 // launchers
 static inline dim3 grid1(int64_t n, int bs = 256) { return dim3((unsigned)cdiv(n, bs)); }
+// samples per workgroup of the kernels that turn E partials through LDS: at
+// least a workgroup per CU where K allows it
+static inline int finish_rows(int64_t K) { return K >= 256 * kFinishRows ? kFinishRows : 16; }
 
 hipError_t launch_term_absmax(const float* t, const float* kcoef, int64_t K, const float* b0, const float* fields,
                               int64_t L, int P, unsigned* tmax, hipStream_t s) {
@@ -1114,7 +1134,7 @@ hipError_t launch_resident(const EncodeShape& sh, const void* P, const void* sda
 hipError_t launch_finish_E_to_m(const float* epart, int nsplit, int64_t HC16, int NB, int64_t K, int G,
                                 const float* unscale, float2* m, hipStream_t s) {
   if (K * G == 0) return hipSuccess;
-  const int rows = K >= 256 * kFinishRows ? kFinishRows : 16;  // at least a workgroup per CU where K allows it
+  const int rows = finish_rows(K);
   hipLaunchKernelGGL(finish_E_to_m_kernel, dim3((unsigned)cdiv(K, rows)), dim3(256), 0, s, epart, nsplit, HC16, NB, K, G,
                      rows, unscale, m);
   return hipGetLastError();
@@ -1179,8 +1199,9 @@ hipError_t launch_grad_b0(const float2* hpart, int nsplit, int64_t HC16, int64_t
 hipError_t launch_grad_kcoef(const float* epart, int nsplit, int64_t HC16, int NB, const float* unscale,
                              const float2* grad_m, int64_t K, int G, int P, int b, float* out, hipStream_t s) {
   if (K == 0) return hipSuccess;
-  hipLaunchKernelGGL(grad_kcoef_kernel, grid1(K), dim3(256), 0, s, epart, nsplit, HC16, NB, unscale, grad_m, K, G, P,
-                     b, out);
+  const int rows = finish_rows(K);
+  hipLaunchKernelGGL(grad_kcoef_kernel, dim3((unsigned)cdiv(K, rows)), dim3(256), 0, s, epart, nsplit, HC16, NB, unscale,
+                     grad_m, K, G, P, b, rows, out);
   return hipGetLastError();
 }
 

@@ -61,9 +61,6 @@ __device__ __forceinline__ float2 sum_strided(const float2* src, int n, int64_t 
 // phase MFMA instructions for P + 1 terms (t*b0 plus P field terms): three
 // split products per term, 32 k-slots per instruction (1, 2 or 3)
 inline int phase_instrs(int n_basis) { return (int)cdiv(3 * (n_basis + 1), 32); }
-// held tiles per wave: 4 while the accumulators stay small (up to 16 coils),
-// else 2 (the default; the autotuner may pick any valid count)
-inline int held_tiles(int nb) { return nb <= 2 ? 4 : 2; }
 // held-tile counts the encode kernel is built for: 2, and 4 up to 4 column
 // blocks (8 blocks x 4 tiles would not fit the register file)
 inline bool valid_held_tiles(int nb, int mt) { return mt == 2 || (mt == 4 && nb <= 4); }
