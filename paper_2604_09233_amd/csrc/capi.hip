@@ -1904,7 +1904,32 @@ extern "C" int nfs_encode_backward(nfs_ctx* ctx, const nfs_problem* prob, const 
                                     at<float>(ws, y.o_unscale), at<void>(ws, y.o_sA), grad_kcoef, c.s),
             "grad_kcoef_fused");
   } else if (grad_kcoef && y.K > 0 && y.P > 0) {
-    for (int b = 0; b < y.P; ++b) {
+    // terms in groups through one E launch each, one by one past the groups
+    char* g = at<char>(ws, y.o_sA);
+    const GradTerms gt = y.L > 0 ? grad_terms(y.prec, y.KC, y.LC, y.G, y.P, y.shE.nsplit, ctx->n_cu, y.total - y.o_sA)
+                                 : GradTerms{1};
+    int b = 0;
+    if (gt.n > 1) {
+      EncodeShape sh = y.shE;
+      sh.NB = gt.NB;
+      sh.MT = gt.MT;
+      sh.nsplit = gt.nsplit;
+      sh.cps = cdiv(y.LC, gt.nsplit);
+      if (scaled_prec(y.prec))
+        NFS_TRY(launch_grad_terms_absmax(gt, r, c.sens, prob->fields, y.L, y.G, y.P, g, c.s), "grad_terms_absmax");
+      for (; y.P - b > 1; b += gt.n) {
+        const int n = std::min(gt.n, y.P - b);
+        NFS_TRY(launch_grad_terms_pack(y.prec, gt, r, c.sens, prob->fields, y.L, y.G, b, n, g, c.s), "grad_terms_pack");
+        float* part = reinterpret_cast<float*>(g + gt.o_part);
+        if ((rc = timed_encode(c, 0, [&] {
+               return launch_encode(sh, at<void>(ws, y.o_sB), at<void>(ws, y.o_vA), g + gt.o_data, part, c.sens, y.L,
+                                    y.G, at<unsigned>(ws, y.o_tmax), y.P + 1, nullptr, c.s);
+             })))
+          return rc;
+        NFS_TRY(launch_grad_terms_finish(y.prec, gt, G, y.K, y.G, y.P, b, n, g, grad_kcoef, c.s), "grad_terms_finish");
+      }
+    }
+    for (; b < y.P; ++b) {
       if ((rc = seq_E(c, r, prob->fields + (int64_t)b * y.L))) return rc;
       NFS_TRY(launch_grad_kcoef(at<float>(ws, y.o_epart), y.shE.nsplit, y.KC * 16, y.NB, unscale_slot(c, 0), G, y.K,
                                 y.G, y.P, b, grad_kcoef, c.s),

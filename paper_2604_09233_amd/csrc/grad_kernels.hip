@@ -351,4 +351,165 @@ hipError_t launch_grad_kcoef_fused(const GradShape& g, const void* heldcoef, con
   return hipGetLastError();
 }
 
+// ---------------------------------------------------------------------------
+// Several field terms per E launch (FP16 and BF16 forms).  The images
+// h_b o rho of a group of terms go through E together as terms x coils
+// virtual coils: the phase tiles and their sine and cosine, most of an E
+// launch at up to 16 coils, are then shared by the group.  Every term keeps
+// the operand it has alone (its own scale included).
+
+// bmax[b][x] = workgroup x's maximum of |h_b| max_c |re|, |im| of S_c rho
+__global__ __launch_bounds__(256) void grad_terms_absmax_kernel(const float2* __restrict__ rho,
+                                                                const float2* __restrict__ sens,
+                                                                const float* __restrict__ fields, int64_t L, int G,
+                                                                int P, float* __restrict__ bmax) {
+  __shared__ unsigned red[kMaxTerms];
+  if (threadIdx.x < kMaxTerms) red[threadIdx.x] = 0u;
+  __syncthreads();
+  for (int64_t l = (int64_t)blockIdx.x * 256 + threadIdx.x; l < L; l += (int64_t)gridDim.x * 256) {
+    float mx = 0.f;
+    const float2 r = rho[l];
+    for (int c = 0; c < G; ++c) {
+      const float2 v = cmul(sens[(int64_t)c * L + l], r);
+      mx = fmaxf(mx, fmaxf(fabsf(v.x), fabsf(v.y)));
+    }
+    for (int b = 0; b < P; ++b) {
+      const float v = fabsf(fields[(int64_t)b * L + l]) * mx;
+      if (v > 0.f) atomicMax(&red[b], __float_as_uint(v));
+    }
+  }
+  __syncthreads();
+  if ((int)threadIdx.x < P) bmax[threadIdx.x * kBmaxBlocks + blockIdx.x] = __uint_as_float(red[threadIdx.x]);
+}
+
+// E operand (layout of pack_data, NB column blocks) of terms b0 .. b0 + n - 1:
+// virtual coil j G + c holds S_c rho h_{b0 + j}
+template <int PREC>
+__global__ __launch_bounds__(256) void grad_terms_pack_kernel(const float2* __restrict__ rho,
+                                                              const float2* __restrict__ sens,
+                                                              const float* __restrict__ fields, int64_t L, int G,
+                                                              int b0, int n, int NB, int64_t LC,
+                                                              const float* __restrict__ bmax,
+                                                              float* __restrict__ unscale, void* __restrict__ out) {
+  __shared__ float scale[kMaxTerms];
+  if (threadIdx.x < kMaxTerms) scale[threadIdx.x] = 1.f;
+  if (PREC != PREC_BF16) {
+    const int lane = threadIdx.x & 63;
+    for (int j = threadIdx.x >> 6; j < n; j += kWaves) {
+      float mx = 0.f;
+      for (int x = lane; x < kBmaxBlocks; x += 64) mx = fmaxf(mx, bmax[(b0 + j) * kBmaxBlocks + x]);
+      for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+      if (lane == 0) {
+        scale[j] = pow2_below(mx, 14);
+        if (blockIdx.x == 0) unscale[j] = 1.f / scale[j];
+      }
+    }
+  }
+  __syncthreads();
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= LC * NB * 64) return;
+  const int lane = (int)(i & 63), g = lane >> 4;
+  const int64_t q = i >> 6, ch = q / NB;
+  const int nb = (int)(q % NB), N = nb * 16 + (lane & 15), v = N >> 1, reim = N & 1;
+  const int j = v / G, c = v - j * G;
+  float vals[8];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int64_t l = ch * kChunk + g * 4 + k;
+    float2 x = make_float2(0.f, 0.f);
+    if (l < L && j < n) {
+      x = cmul(sens[(int64_t)c * L + l], rho[l]);
+      const float w = fields[(int64_t)(b0 + j) * L + l] * scale[j];
+      x.x *= w;
+      x.y *= w;
+    }
+    vals[2 * k] = reim ? x.y : x.x;
+    vals[2 * k + 1] = reim ? x.x : -x.y;
+  }
+  store_fragment<PREC>(vals, out, ch, nb, NB, lane);
+}
+
+// out[k][b0 + j] = Im sum_c G_c(k) conj(Z_jc(k)) from the group's E partials
+// (16 samples per workgroup, turned through LDS; coils added in order)
+__global__ __launch_bounds__(256) void grad_terms_finish_kernel(const float* __restrict__ epart, int nsplit,
+                                                                int64_t HC16, int NB, const float* __restrict__ unscale,
+                                                                const float2* __restrict__ grad_m, int64_t K, int G,
+                                                                int P, int b0, int n, float* __restrict__ out) {
+  constexpr int kRows = 16;
+  __shared__ float tile[64][kRows + 1];
+  const int64_t k0 = (int64_t)blockIdx.x * kRows;
+  const int nc = NB * 8;
+  for (int i = threadIdx.x; i < kRows * nc; i += 256) {
+    const int r = i / nc, v = i - r * nc;
+    if (v >= n * G || k0 + r >= K) continue;
+    const float2 z = sum_strided((const float2*)epart + (k0 + r) * nc + v, nsplit, HC16 * nc);
+    const float2 g = grad_m[(int64_t)(v % G) * K + k0 + r];
+    tile[v][r] = g.y * z.x - g.x * z.y;
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < kRows * n; i += 256) {
+    const int r = i / n, j = i - r * n;
+    if (k0 + r >= K) continue;
+    float acc = 0.f;
+    for (int c = 0; c < G; ++c) acc += tile[j * G + c][r];
+    out[(k0 + r) * P + b0 + j] = acc * (unscale ? unscale[j] : 1.f);
+  }
+}
+
+GradTerms grad_terms(int prec, int64_t KC, int64_t LC, int G, int P, int nsplit, int n_cu, size_t avail) {
+  GradTerms t{};
+  auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
+  for (int n = std::min(64 / G, P); n > 1; --n) {
+    t.n = n;
+    t.NB = col_blocks(n * G);
+    t.MT = t.NB <= 4 ? 4 : 2;
+    t.o_bmax = 0;
+    t.o_unscale = al((size_t)kMaxTerms * kBmaxBlocks * 4);
+    t.o_data = t.o_unscale + 256;
+    t.o_part = t.o_data + al((size_t)LC * t.NB * data_chunk_bytes(prec));
+    const size_t one = (size_t)KC * kChunk * t.NB * 16 * 4;
+    if (avail < t.o_part + one) continue;
+    // as many splits as a single term's launch where they fit; fewer are
+    // fine while there are four workgroups per CU
+    const int64_t gx = cdiv(KC, (int64_t)kWaves * t.MT);
+    const int64_t fit = (int64_t)((avail - t.o_part) / one);
+    t.nsplit = (int)std::min<int64_t>(nsplit, fit);
+    if (t.nsplit < nsplit && gx * t.nsplit < 4LL * n_cu) continue;
+    return t;
+  }
+  t.n = 1;
+  return t;
+}
+
+hipError_t launch_grad_terms_absmax(const GradTerms& t, const float2* rho, const float2* sens, const float* fields,
+                                    int64_t L, int G, int P, char* ws, hipStream_t s) {
+  hipLaunchKernelGGL(grad_terms_absmax_kernel, dim3(kBmaxBlocks), dim3(256), 0, s, rho, sens, fields, L, G, P,
+                     (float*)(ws + t.o_bmax));
+  return hipGetLastError();
+}
+
+hipError_t launch_grad_terms_pack(int prec, const GradTerms& t, const float2* rho, const float2* sens,
+                                  const float* fields, int64_t L, int G, int b0, int n, char* ws, hipStream_t s) {
+  const int64_t LC = cdiv(L, kChunk);
+  const dim3 gr((unsigned)cdiv(LC * t.NB * 64, 256)), bl(256);
+  const float* bmax = (const float*)(ws + t.o_bmax);
+  float* un = (float*)(ws + t.o_unscale);
+  if (prec == PREC_BF16)
+    hipLaunchKernelGGL(grad_terms_pack_kernel<PREC_BF16>, gr, bl, 0, s, rho, sens, fields, L, G, b0, n, t.NB, LC, bmax,
+                       un, ws + t.o_data);
+  else
+    hipLaunchKernelGGL(grad_terms_pack_kernel<PREC_FP16>, gr, bl, 0, s, rho, sens, fields, L, G, b0, n, t.NB, LC, bmax,
+                       un, ws + t.o_data);
+  return hipGetLastError();
+}
+
+hipError_t launch_grad_terms_finish(int prec, const GradTerms& t, const float2* grad_m, int64_t K, int G, int P, int b0,
+                                    int n, char* ws, float* out, hipStream_t s) {
+  const int64_t KC = cdiv(K, kChunk);
+  hipLaunchKernelGGL(grad_terms_finish_kernel, dim3((unsigned)KC), dim3(256), 0, s, (const float*)(ws + t.o_part),
+                     t.nsplit, KC * kChunk, t.NB, prec == PREC_BF16 ? nullptr : (const float*)(ws + t.o_unscale), grad_m,
+                     K, G, P, b0, n, out);
+  return hipGetLastError();
+}
+
 }  // namespace nfs

@@ -192,6 +192,21 @@ hipError_t launch_grad_kcoef_fused(const GradShape& g, const void* heldcoef, con
                                    int G, int P, int NQ, const unsigned* tmax, float* bmax, float* unscale, void* ws,
                                    float* out, hipStream_t s);
 
+// Several terms per E launch (FP16, BF16): group size n (1: not offered), column
+// blocks, held tiles and splits of its E launches, offsets in a buffer of
+// `avail` bytes
+struct GradTerms {
+  int n, NB, MT, nsplit;
+  size_t o_bmax, o_unscale, o_data, o_part;
+};
+GradTerms grad_terms(int prec, int64_t KC, int64_t LC, int G, int P, int nsplit, int n_cu, size_t avail);
+hipError_t launch_grad_terms_absmax(const GradTerms& t, const float2* rho, const float2* sens, const float* fields,
+                                    int64_t L, int G, int P, char* ws, hipStream_t s);
+hipError_t launch_grad_terms_pack(int prec, const GradTerms& t, const float2* rho, const float2* sens,
+                                  const float* fields, int64_t L, int G, int b0, int n, char* ws, hipStream_t s);
+hipError_t launch_grad_terms_finish(int prec, const GradTerms& t, const float2* grad_m, int64_t K, int G, int P, int b0,
+                                    int n, char* ws, float* out, hipStream_t s);
+
 // ---- stopping-criteria instrumentation (quality_kernels.hip) ------------------
 // mean SSIM of |imgs[i]| against |ref| for i < n_img into out[i] (float64);
 // images [n_img][L] complex, L = nx ny nz (x fastest); needs nx, ny >= 11 and

@@ -70,3 +70,22 @@ def test_fused_kcoef_gradient_zero_and_repeat():
     a = nfs.encode_backward(gp, rho, m, "fp32")
     b = nfs.encode_backward(gp, rho, m, "fp32")
     assert all(torch.equal(x, y) for x, y in zip(a, b))
+
+
+@pytest.mark.parametrize("prec", ["fp16", "bf16"])
+@pytest.mark.parametrize("L,K,G,P", [(1000, 700, 4, 16), (333, 257, 16, 17), (900, 500, 21, 9), (700, 300, 32, 5),
+                                     (500, 200, 33, 4), (64, 48, 1, 31), (40, 20, 2, 2), (3000, 2000, 15, 16)])
+def test_grouped_kcoef_gradient(prec, L, K, G, P):
+    """The half-precision forms take several terms per E launch where their
+    coils fit 64 virtual ones (groups, a shorter last group, a single last
+    term, no group at all): at the operand rounding's bar."""
+    from paper_2604_09233_amd import nfs
+
+    d = synth.random_problem(L, K, G, P, seed=93, phase_scale=8.0)
+    gp = nfs.Problem(d["sens"], d["fields"], d["b0"], d["kcoef"], d["t"])
+    gk = nfs.encode_backward(gp, torch.from_numpy(d["rho"]), torch.from_numpy(d["m"]), prec, False, False, True)[2]
+    ref = reference(d, d["m"])
+    got = gk.cpu().numpy().astype(np.float64)
+    per_term = np.linalg.norm(got - ref, axis=0) / np.linalg.norm(ref, axis=0)
+    print(f"grouped grad_kcoef {prec} L={L} K={K} G={G} P={P}: worst term {per_term.max():.1e}")
+    assert per_term.max() < 4e-3  # 2e-3 operand bar; single small terms may stand at twice the whole's error
