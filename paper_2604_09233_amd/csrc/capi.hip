@@ -450,23 +450,55 @@ static int timed_encode(const Ctx& c, int kind, F&& launch) {
   return NFS_OK;
 }
 
-static int seq_pack_coefs(const Ctx& c, bool forE, bool forH) {
+// What stands before a call's first encode launch: the term maxima, the phase
+// parts for E and / or E^H and, with src, the data operand of `data_op` (E:
+// src = rho; E^H: src = m [G][K]) with its maximum.
+static int seq_setup(const Ctx& c, bool forE, bool forH, int data_op = OP_E, const float2* src = nullptr) {
   const Layout& y = c.y;
   const nfs_problem* p = c.pr;
   unsigned* tmax = at<unsigned>(c.ws, y.o_tmax);
-  NFS_TRY(launch_term_absmax(p->t, p->kcoef, y.K, p->b0, p->fields, y.L, y.P, tmax, c.s), "term_absmax");
+  float* bmax = at<float>(c.ws, y.o_bmax);
+  const bool E = data_op == OP_E;
+  const float2* mul = E ? c.sens : nullptr;
+  const int64_t n = E ? y.L : y.K, cs = E ? 0 : y.K;
+  const float2* mx = src && scaled_prec(y.prec) ? src : nullptr;
+  // One launch while its few workgroups are faster than three launches on the
+  // whole chip (16 terms, 8 coils, FP16, voxels x samples; three -> one):
+  // 512 x 512 E 27.3 -> 21.6 us, 16384 x 64 E 36.4 -> 27.1, 64 x 16384 E^H
+  // 34.3 -> 33.1; past the line 64 x 32768 E 31.2 -> 36.4, E^H 42.9 -> 50.4.
+  if (std::max(y.K, y.L) <= kSmallItems) {
+    NFS_TRY(launch_maxima_small(p->t, p->kcoef, y.K, p->b0, p->fields, y.L, y.P, tmax, mx, mul, n, 1, cs, y.G, bmax, c.s),
+            "maxima");
+  } else {
+    NFS_TRY(launch_term_absmax(p->t, p->kcoef, y.K, p->b0, p->fields, y.L, y.P, tmax, c.s), "term_absmax");
+    if (mx) NFS_TRY(launch_absmax(mx, mul, nullptr, n, 1, cs, y.G, bmax, nullptr, c.s), "absmax");
+  }
+  SetupPack a{};
+  a.tmax = tmax;
+  a.P = y.P;
+  a.NQ = y.NQ;
   if (forE) {
-    NFS_TRY(launch_pack_phase(p->b0, p->fields, y.L, y.P, 1, 0, y.NQ, tmax, at<void>(c.ws, y.o_vA), c.s),
-            "pack_phase");
-    NFS_TRY(launch_pack_phase(p->t, p->kcoef, y.K, y.P, 0, 1, y.NQ, tmax, at<void>(c.ws, y.o_sB), c.s),
-            "pack_phase");
+    a.ph[a.nph++] = PhaseSide{p->b0, p->fields, y.L, 1, 0, at<void>(c.ws, y.o_vA)};
+    a.ph[a.nph++] = PhaseSide{p->t, p->kcoef, y.K, 0, 1, at<void>(c.ws, y.o_sB)};
   }
   if (forH) {
-    NFS_TRY(launch_pack_phase(p->t, p->kcoef, y.K, y.P, 0, 0, y.NQ, tmax, at<void>(c.ws, y.o_sA), c.s),
-            "pack_phase");
-    NFS_TRY(launch_pack_phase(p->b0, p->fields, y.L, y.P, 1, 1, y.NQ, tmax, at<void>(c.ws, y.o_vB), c.s),
-            "pack_phase");
+    a.ph[a.nph++] = PhaseSide{p->t, p->kcoef, y.K, 0, 0, at<void>(c.ws, y.o_sA)};
+    a.ph[a.nph++] = PhaseSide{p->b0, p->fields, y.L, 1, 1, at<void>(c.ws, y.o_vB)};
   }
+  a.G = y.G;
+  a.NB = y.NB;
+  if (src) {
+    a.src = src;
+    a.mul = mul;
+    a.n_items = n;
+    a.is = 1;
+    a.cs = cs;
+    a.nchunks = E ? y.LC : y.KC;
+    a.out = at<void>(c.ws, E ? y.o_dataE : y.o_dataH);
+    a.bmax = bmax;
+    a.unscale = at<float>(c.ws, y.o_unscale) + (E ? 0 : 1);
+  }
+  NFS_TRY(launch_setup_pack(data_op, y.prec, a, c.s), "setup_pack");
   return NFS_OK;
 }
 
@@ -509,12 +541,9 @@ static int mid_EHE(const Ctx& c, const float* wgt = nullptr, float wmul = 1.f) {
   return NFS_OK;
 }
 
-// E part: rho -> epart (partials) via packed Q = S o rho (o wgt);
-// bmax_ready: the FP16 scale bound of Q is already in bmax
-static int seq_E(const Ctx& c, const float2* rho, const float* wgt = nullptr, bool bmax_ready = false) {
+// The encode launches of E and E^H on packed operands.
+static int enc_E(const Ctx& c) {
   const Layout& y = c.y;
-  int rc = pre_E(c, rho, bmax_ready, wgt);
-  if (rc) return rc;
   return timed_encode(c, 0, [&] {
     if (c.PE)
       return launch_resident(y.shE, c.PE, at<void>(c.ws, y.o_dataE), at<float>(c.ws, y.o_epart), c.sens, y.L, y.G,
@@ -525,11 +554,8 @@ static int seq_E(const Ctx& c, const float2* rho, const float* wgt = nullptr, bo
   });
 }
 
-// E^H part: src (m [G][K]) (o wgt) -> hpart (coil-combined partials)
-static int seq_EH(const Ctx& c, const float2* src, int64_t is, int64_t cs, const float* wgt = nullptr) {
+static int enc_H(const Ctx& c) {
   const Layout& y = c.y;
-  int rc = pre_EH(c, src, is, cs, wgt);
-  if (rc) return rc;
   return timed_encode(c, 1, [&] {
     if (c.PH)
       return launch_resident(y.shH, c.PH, at<void>(c.ws, y.o_dataH), at<float>(c.ws, y.o_hpart), c.sens, y.L, y.G,
@@ -540,22 +566,29 @@ static int seq_EH(const Ctx& c, const float2* src, int64_t is, int64_t cs, const
   });
 }
 
+// E part: rho -> epart (partials) via packed Q = S o rho (o wgt);
+// bmax_ready: the FP16 scale bound of Q is already in bmax
+static int seq_E(const Ctx& c, const float2* rho, const float* wgt = nullptr, bool bmax_ready = false) {
+  int rc = pre_E(c, rho, bmax_ready, wgt);
+  if (rc) return rc;
+  return enc_E(c);
+}
+
+// E^H part: src (m [G][K]) (o wgt) -> hpart (coil-combined partials)
+static int seq_EH(const Ctx& c, const float2* src, int64_t is, int64_t cs, const float* wgt = nullptr) {
+  int rc = pre_EH(c, src, is, cs, wgt);
+  if (rc) return rc;
+  return enc_H(c);
+}
+
 // E^H E: p -> hpart; the E^H operand is packed straight from the E partials
 // (optionally weighted per sample: E^H diag(wgt * wmul) E)
 static int seq_EHE(const Ctx& c, const float2* p, bool bmax_ready = false, const float* wgt = nullptr,
                    float wmul = 1.f) {
-  const Layout& y = c.y;
   int rc = seq_E(c, p, nullptr, bmax_ready);
   if (rc) return rc;
   if ((rc = mid_EHE(c, wgt, wmul))) return rc;
-  return timed_encode(c, 1, [&] {
-    if (c.PH)
-      return launch_resident(y.shH, c.PH, at<void>(c.ws, y.o_dataH), at<float>(c.ws, y.o_hpart), c.sens, y.L, y.G,
-                             c.stop, c.s);
-    return launch_encode(y.shH, at<void>(c.ws, y.o_vB), at<void>(c.ws, y.o_sA), at<void>(c.ws, y.o_dataH),
-                         at<float>(c.ws, y.o_hpart), c.sens, y.L, y.G, at<unsigned>(c.ws, y.o_tmax), y.P + 1, c.stop,
-                         c.s);
-  });
+  return enc_H(c);
 }
 
 extern "C" int nfs_apply_E(nfs_ctx* ctx, const nfs_problem* prob, const float* rho, float* m, int precision,
@@ -571,8 +604,8 @@ extern "C" int nfs_apply_E(nfs_ctx* ctx, const nfs_problem* prob, const float* r
   if ((rc = check_ws(y, ws, ws_bytes, fn))) return rc;
   if (y.K == 0) return NFS_OK;
   Ctx c{ctx, y, prob, reinterpret_cast<const float2*>(prob->sens), ws, (hipStream_t)stream, nullptr};
-  if ((rc = seq_pack_coefs(c, true, false))) return rc;
-  if ((rc = seq_E(c, reinterpret_cast<const float2*>(rho)))) return rc;
+  if ((rc = seq_setup(c, true, false, OP_E, reinterpret_cast<const float2*>(rho)))) return rc;
+  if ((rc = enc_E(c))) return rc;
   NFS_TRY(launch_finish_E_to_m(at<float>(ws, y.o_epart), y.shE.nsplit, y.KC * 16, y.NB, y.K, y.G, unscale_slot(c, 0),
                                reinterpret_cast<float2*>(m), c.s),
           "finish_E_to_m");
@@ -592,8 +625,8 @@ extern "C" int nfs_apply_EH(nfs_ctx* ctx, const nfs_problem* prob, const float* 
   if ((rc = check_ws(y, ws, ws_bytes, fn))) return rc;
   if (y.L == 0) return NFS_OK;
   Ctx c{ctx, y, prob, reinterpret_cast<const float2*>(prob->sens), ws, (hipStream_t)stream, nullptr};
-  if ((rc = seq_pack_coefs(c, false, true))) return rc;
-  if ((rc = seq_EH(c, reinterpret_cast<const float2*>(m), 1, y.K))) return rc;
+  if ((rc = seq_setup(c, false, true, OP_EH, reinterpret_cast<const float2*>(m)))) return rc;
+  if ((rc = enc_H(c))) return rc;
   NFS_TRY(launch_finish_EH(at<float2>(ws, y.o_hpart), y.shH.nsplit, y.LC * 16, y.L, unscale_slot(c, 1),
                            reinterpret_cast<float2*>(x), c.s),
           "finish_EH");
@@ -613,8 +646,10 @@ extern "C" int nfs_apply_EHE(nfs_ctx* ctx, const nfs_problem* prob, const float*
   if ((rc = check_ws(y, ws, ws_bytes, fn))) return rc;
   if (y.L == 0) return NFS_OK;
   Ctx c{ctx, y, prob, reinterpret_cast<const float2*>(prob->sens), ws, (hipStream_t)stream, nullptr};
-  if ((rc = seq_pack_coefs(c, true, true))) return rc;
-  if ((rc = seq_EHE(c, reinterpret_cast<const float2*>(p)))) return rc;
+  if ((rc = seq_setup(c, true, true, OP_E, reinterpret_cast<const float2*>(p)))) return rc;
+  if ((rc = enc_E(c))) return rc;
+  if ((rc = mid_EHE(c))) return rc;
+  if ((rc = enc_H(c))) return rc;
   NFS_TRY(launch_finish_EH(at<float2>(ws, y.o_hpart), y.shH.nsplit, y.LC * 16, y.L, unscale_slot(c, 1),
                            reinterpret_cast<float2*>(q), c.s),
           "finish_EH");
@@ -684,7 +719,7 @@ static int run_cg(nfs_ctx* ctx, const nfs_problem* prob, const Layout& y, const 
   const int ns = y.shH.nsplit;
 
   NFS_TRY(launch_cg_reset(st, s), "cg_reset");
-  if ((rc = seq_pack_coefs(c, true, true))) return rc;
+  if ((rc = seq_setup(c, true, true, OP_EH, reinterpret_cast<const float2*>(m)))) return rc;
   if (resident) {
     const unsigned* tmax = at<unsigned>(ws, y.o_tmax);
     NFS_TRY(launch_build_P(y.NQ, at<void>(ws, y.o_sB), at<void>(ws, y.o_vA), y.KC, y.LC, tmax, y.P + 1,
@@ -697,7 +732,7 @@ static int run_cg(nfs_ctx* ctx, const nfs_problem* prob, const Layout& y, const 
     c.PH = at<void>(ws, y.o_PH);
   }
   NFS_TRY(launch_cg_norm_m(st, reinterpret_cast<const float2*>(m), (int64_t)y.G * y.K, s), "cg_norm_m");
-  if ((rc = seq_EH(c, reinterpret_cast<const float2*>(m), 1, y.K))) return rc;
+  if ((rc = enc_H(c))) return rc;
   NFS_TRY(launch_cg_init(st, hpart, ns, hstride, unscale_slot(c, 1), x, y.L, s), "cg_init");
   NFS_TRY(launch_cg_start(st, n_iter, s), "cg_start");
   if (reorth) NFS_TRY(launch_cg_store_v(st, 0, s), "cg_store_v");
@@ -1724,10 +1759,10 @@ static int run_cg_lockstep(nfs_ctx* ctx, int n, const nfs_problem* probs, const 
     if (scaled_prec(y.prec)) NFS_TRY(launch_sens_absmax(r.sens, y.G, y.L, at<float>(r.ws, y.o_smax), sk), "sens_absmax");
     NFS_TRY(launch_cg_reset(r.st, sk), "cg_reset");
     Ctx c = ctx_of(r, sk);
-    int e = seq_pack_coefs(c, true, true);
+    int e = seq_setup(c, true, true, OP_EH, reinterpret_cast<const float2*>(r.m));
     if (e) return e;
     NFS_TRY(launch_cg_norm_m(r.st, reinterpret_cast<const float2*>(r.m), (int64_t)y.G * y.K, sk), "cg_norm_m");
-    return pre_EH(c, reinterpret_cast<const float2*>(r.m), 1, y.K);
+    return NFS_OK;
   });
   if (rc) return rc;
   if ((rc = persistent_encode(ctx, runs, OP_EH, counters, s))) return rc;
@@ -1885,7 +1920,7 @@ extern "C" int nfs_encode_backward(nfs_ctx* ctx, const nfs_problem* prob, const 
   Ctx c{ctx, y, prob, reinterpret_cast<const float2*>(prob->sens), ws, (hipStream_t)stream, nullptr};
   const float2* G = reinterpret_cast<const float2*>(grad_m);
   const float2* r = reinterpret_cast<const float2*>(rho);
-  if ((rc = seq_pack_coefs(c, grad_kcoef != nullptr && y.P > 0, grad_rho != nullptr || grad_b0 != nullptr))) return rc;
+  if ((rc = seq_setup(c, grad_kcoef != nullptr && y.P > 0, grad_rho != nullptr || grad_b0 != nullptr))) return rc;
   if (grad_rho && y.L > 0) {
     if ((rc = seq_EH(c, G, 1, y.K))) return rc;
     NFS_TRY(launch_finish_EH(at<float2>(ws, y.o_hpart), y.shH.nsplit, y.LC * 16, y.L, unscale_slot(c, 1),
@@ -2019,7 +2054,7 @@ struct TuneSlice {
 static int tune_prepare(nfs_ctx* ctx, const TuneSlice& t, hipStream_t s) {
   const Layout& y = t.tl.y;
   Ctx c{ctx, y, t.pr, reinterpret_cast<const float2*>(t.pr->sens), t.ws, s, nullptr};
-  int rc = seq_pack_coefs(c, true, true);
+  int rc = seq_setup(c, true, true);
   if (rc) return rc;
   float2* ones = at<float2>(t.ws, t.tl.o_ones);
   NFS_TRY(launch_fill(reinterpret_cast<float*>(ones), 2 * y.L, 1.f, s), "fill");

@@ -130,10 +130,39 @@ hipError_t launch_encode_persistent(int op, int prec, int NQ, int NB, int MT, co
 // fields[b]); clears tmax first
 hipError_t launch_term_absmax(const float* t, const float* kcoef, int64_t K, const float* b0, const float* fields,
                               int64_t L, int P, unsigned* tmax, hipStream_t s);
-// side 0: samples (c0 = t, cb = kcoef [K][P]); side 1: voxels (c0 = b0, cb = fields [P][L]);
-// role 0: streamed side (MFMA operand A), role 1: held side (operand B)
-hipError_t launch_pack_phase(const float* c0, const float* cb, int64_t n_items, int P, int side, int role, int NQ,
-                             const unsigned* tmax, void* out, hipStream_t s);
+// the same maxima in one launch for small calls, without clearing; src (or
+// NULL): also the data maxima of launch_absmax (no weight) into bmax
+constexpr int64_t kSmallItems = 16384;  // samples and voxels of a small call
+hipError_t launch_maxima_small(const float* t, const float* kcoef, int64_t K, const float* b0, const float* fields,
+                               int64_t L, int P, unsigned* tmax, const float2* src, const float2* mul, int64_t n_items,
+                               int64_t is, int64_t cs, int G, float* bmax, hipStream_t s);
+// One side's phase parts: side 0: samples (c0 = t, cb = kcoef [K][P]); side 1:
+// voxels (c0 = b0, cb = fields [P][L]); role 0: streamed side (MFMA operand
+// A), role 1: held side (operand B)
+struct PhaseSide {
+  const float* c0;
+  const float* cb;
+  int64_t n_items;
+  int side, role;
+  void* out;
+};
+// The packing in front of a call's first encode launch: nph phase sides, then
+// the data operand of launch_pack_data without weight (nchunks 0: none).
+struct SetupPack {
+  PhaseSide ph[4];
+  int64_t first[5];  // filled by the launcher
+  const unsigned* tmax;
+  int nph, P, NQ;
+  int G, NB;
+  const float2* src;
+  const float2* mul;
+  int64_t n_items, is, cs, nchunks;
+  void* out;
+  const float* bmax;
+  float* unscale;
+  const int* stop;
+};
+hipError_t launch_setup_pack(int op, int prec, SetupPack a, hipStream_t s);
 hipError_t launch_scale_sens(const float2* sens, const float* icorr, int G, int64_t L, float2* out,
                              hipStream_t s);
 // value(item, c) = src[item*is + c*cs] * (mul ? mul[c*n_items + item] : 1) * (wgt ? wgt[item] : 1)
