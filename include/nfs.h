@@ -233,8 +233,9 @@ int nfs_lcurve_corner(const double* hist, int n_rows, int* corner, double* kappa
  * order, bin (u, v, w) standing for the signed frequency u (if u < ceil(nx/2),
  * else u - nx) and so on, in cycles per field of view.  The DFT is applied
  * one axis at a time (float32 sums, twiddles from double precision): forward
- * passes, then f and 1/L, then inverse passes, L (nx + ny + nz) complex
- * multiply-adds per direction.  rho, out: device [L] complex (must not
+ * passes, then f and 1/L, then inverse passes, n complex multiply-adds per
+ * value and pass, or n1 + n2 where the axis has fitting factors n = n1 n2
+ * (the two passes of the last axis are then one).  rho, out: device [L] complex (must not
  * alias); f: device float [L].  Each axis at most 2048 long (NFS_ESHAPE
  * otherwise).  Workspace: nfs_kspace_filter_workspace_bytes (L complex,
  * rounded up to 256 bytes; ctx is not read).                              */

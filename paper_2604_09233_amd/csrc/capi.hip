@@ -1065,15 +1065,32 @@ extern "C" int nfs_apply_kspace_filter(nfs_ctx* ctx, const float* rho, float* ou
     NFS_TRY(launch_filter_scale(src, dst_out, f, inv_l, L, s), "filter_scale");
     return NFS_OK;
   }
-  const int passes = 2 * (int)axes.size();
-  for (int i = 0; i < passes; ++i) {
-    const bool fwd = i < (int)axes.size();
-    const Axis& ax = fwd ? axes[i] : axes[passes - 1 - i];
-    const bool last_fwd = i + 1 == (int)axes.size();
+  // forward passes, then the inverse ones in the other order, alternating
+  // between ws and out so that the last lands in out; the two passes of the
+  // last axis are one in-place launch where its plan has two factors
+  const int A = (int)axes.size();
+  std::vector<DftPlan> plan;
+  for (const Axis& ax : axes) plan.push_back(dft_plan(ax.n, ax.outer, ax.inner));
+  const bool mid = plan[A - 1].two;
+  const int passes = 2 * (mid ? A - 1 : A);
+  for (int i = 0; i <= passes; ++i) {
+    if (mid && i == passes / 2) {
+      const Axis& ax = axes[A - 1];
+      float2* dst = A == 1 ? dst_out : const_cast<float2*>(src);
+      NFS_TRY(launch_dft_two(src, dst, ax.outer, ax.inner, plan[A - 1], -1, inv_l, f, s), "dft_two");
+    }
+    if (i == passes) break;
+    const bool fwd = i < passes / 2;
+    const int k = fwd ? i : passes - 1 - i;
+    const Axis& ax = axes[k];
+    const bool last_fwd = !mid && i + 1 == A;
     float2* dst = (passes - 1 - i) % 2 == 0 ? dst_out : dst_ws;
-    NFS_TRY(launch_dft_axis(src, dst, ax.outer, ax.n, ax.inner, fwd ? -1 : +1, last_fwd ? inv_l : 1.f,
-                            last_fwd ? f : nullptr, s),
-            "dft_axis");
+    if (plan[k].two)
+      NFS_TRY(launch_dft_two(src, dst, ax.outer, ax.inner, plan[k], fwd ? -1 : +1, 1.f, nullptr, s), "dft_two");
+    else
+      NFS_TRY(launch_dft_axis(src, dst, ax.outer, ax.n, ax.inner, fwd ? -1 : +1, last_fwd ? inv_l : 1.f,
+                              last_fwd ? f : nullptr, s),
+              "dft_axis");
     src = dst;
   }
   return NFS_OK;

@@ -251,6 +251,19 @@ hipError_t launch_ssim(const float2* imgs, int n_img, const float2* ref, int nx,
 constexpr int kMaxDftAxis = 2048;
 hipError_t launch_dft_axis(const float2* in, float2* out, int64_t outer, int n, int64_t inner, int sign, float scale,
                            const float* f, hipStream_t s);
+// The pass as two short sums per output (n = n1 n2), where `two` says that it
+// pays: no scale; with f: sign pass, times f * scale, pass of the other sign.
+// in == out is allowed.
+struct DftPlan {
+  int n, n1, n2, lw;      // lw: log2 of a workgroup's columns
+  unsigned m, m1, m2;     // division by n, n1, n2
+  bool two;
+  int64_t blocks;
+  size_t lds;
+};
+DftPlan dft_plan(int n, int64_t outer, int64_t inner);
+hipError_t launch_dft_two(const float2* in, float2* out, int64_t outer, int64_t inner, const DftPlan& p, int sign,
+                          float scale, const float* f, hipStream_t s);
 hipError_t launch_filter_scale(const float2* in, float2* out, const float* f, float scale, int64_t L, hipStream_t s);
 
 // ---- phase-basis compression on the device (compress_kernels.hip) ----------

@@ -427,7 +427,7 @@ def phase_shift(m, theta, sign: int, out=None):
 
 def apply_kspace_filter(rho, f, dims, device: int = 0):
     """IFFT(FFT(rho) o f) on the image grid dims (x fastest), on the GPU,
-    one DFT pass per axis and direction (see include/nfs.h)."""
+    one DFT pass per axis and direction (see include/nfs.h for the sums)."""
     dev = torch.device("cuda", device)
     rho = _c64(rho, dev)
     f = f.to(device=dev, dtype=torch.float32).contiguous() if torch.is_tensor(f) else \
