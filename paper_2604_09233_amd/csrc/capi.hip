@@ -306,10 +306,21 @@ static EncodeShape encode_shape(const nfs_ctx* ctx, const nfs_problem* pr, int o
     const int big = valid_held_tiles(NB, 4) ? 4 : 2;
     const bool solve = call == NFS_OP_CG || call == NFS_OP_CG_RESIDENT;
     ns = solve ? solve_split(HC, SC, NB, n_cu) : operator_split(op, HC, SC, NB, big, n_cu, call != NFS_OP_EHE);
-    // four held tiles read each staged chunk half as often as two, which
-    // pays once two workgroups per CU are left (48x48x24, 32 coils: E 648 ->
-    // 590 us; 64x64, 8 coils, 12 000 samples, 1.5 per CU: two are 10 % faster)
-    MT = cdiv(HC, (int64_t)kWaves * big) * ns >= 2 * n_cu ? big : 2;
+    // Four held tiles read each staged chunk half as often as two, but a
+    // last round of workgroups that leaves most CUs idle lasts twice as long.
+    // So four from two workgroups per CU on (48x48x24, 32 coils: E 648 -> 590
+    // us; 64x64, 8 coils, 12 000 samples, 1.5 per CU: two are 10 % faster),
+    // unless fewer than eight per CU end up to half a round past a whole one:
+    // time of four over two at 2.00 / 2.03 / 2.45 / 2.75 per CU, 32 coils,
+    // E^H FP32 0.91 / 1.13 / 1.08, E FP32 0.96 / 1.07 / - / 0.95; 12 coils,
+    // 4.00 / 4.06 / 4.29, E^H FP16 0.96 / 1.09 / 1.05.  E in BF16, and in FP16
+    // up to 16 coils, has no coil sums and little to wait for there (2.03:
+    // 0.97, 2.75: 0.90; 4.12: 0.98) and keeps four.
+    const int64_t w4 = cdiv(HC, (int64_t)kWaves * big) * ns, w2 = cdiv(HC, (int64_t)kWaves * 2) * ns;
+    const int64_t cu = n_cu > 0 ? n_cu : 1;
+    const bool light = op == OP_E && (prec == PREC_BF16 || (prec == PREC_FP16 && NB <= 2));
+    const bool tail = !light && w4 < 8 * cu && 2 * cdiv(w4, cu) > cdiv(w2, cu);
+    MT = w4 >= 2 * cu && !tail ? big : 2;
   }
   EncodeShape sh{op, prec, NQ, NB, MT, HC, SC, ns, 0};
   sh.cps = cdiv(SC, ns > 0 ? ns : 1);
