@@ -264,18 +264,18 @@ static int solve_split(int64_t held_chunks, int64_t strm_chunks, int NB, int n_c
 
 // Default split count of single operators (E, E^H, E^H E, backward): more
 // workgroups than the resident ones even out their uneven ends, so E aims at
-// 13 per CU (at least 32 chunks each; 64 past 16 coils, whose partials are
-// as large again) and E^H, whose workgroups end in the
-// coil sums, at 8 (at least 64 chunks), never below the solves' count.
+// 13 per CU (at least 32 chunks each; 64 past 16 coils, whose partials are as
+// large again) and E^H, whose workgroups end in the coil sums, at 8 (at least
+// 64 chunks), never below the solves' count.
 // Measured (fp16 / fp32, us, solves' count -> this): 200x200, 16 coils, 90 000
 // samples E 1008 -> 822 / 1997 -> 1640, E^H 895 -> 865; 48x48x24, 32 coils,
 // 32 000 samples E 648 -> 554 / 1375 -> 1255, E^H 731 -> 596; 128x128, 16
 // coils, 60 000 samples E 265 -> 237, E^H 247 -> 244.  64 chunks instead of 32:
 // 128x128, 32 coils, 30 000 samples E^H E 498 -> 486 (solves' count 486),
 // 12 000 samples E 118 -> 109; 100x100, 30 000 samples, FP32 E 293 -> 307
-// (solves' count 390).  Where even that leaves
-// CUs idle, a call of one direction (`alone`) goes down to 8 chunks a split,
-// as long as E's partials stay small (32x32, 2048 samples: E call 43 -> 37).
+// (solves' count 390).  Where even that leaves CUs idle, a call of one
+// direction (`alone`) goes down to 8 chunks a split, as long as E's partials
+// stay small (32x32, 2048 samples: E call 43 -> 37).
 static int operator_split(int op, int64_t held_chunks, int64_t strm_chunks, int NB, int MT, int n_cu, bool alone) {
   const int base = solve_split(held_chunks, strm_chunks, NB, n_cu);
   const int64_t gx = cdiv(held_chunks, (int64_t)kWaves * MT);

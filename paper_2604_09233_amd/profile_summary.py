@@ -22,7 +22,7 @@ from collections import defaultdict
 HERE = os.path.dirname(os.path.abspath(__file__))
 TRAFFIC_TAG = "encode-kernel traffic per launch (bytes):"
 # what the encode kernels' machine code depends on: their source file, the
-# part of the shared header before the launcher declarations (constants,
+# fragment layouts and phase tile it includes, the part of the shared header before the launcher declarations (constants,
 # shape and work-list structs, the split-sum helper), and the compiler flags
 # they are built with
 _HEADER_END = "// ---- launchers (encode_kernels.hip)"
@@ -32,8 +32,9 @@ def kernel_source_hash() -> str:
     from . import build
 
     h = hashlib.sha256()
-    with open(os.path.join(HERE, "csrc", "encode_kernels.hip"), "rb") as f:
-        h.update(f.read())
+    for src in ("encode_kernels.hip", "fragment.h"):
+        with open(os.path.join(HERE, "csrc", src), "rb") as f:
+            h.update(f.read())
     with open(os.path.join(HERE, "csrc", "nfs_internal.h")) as f:
         hdr = f.read()
     h.update(hdr[:hdr.index(_HEADER_END)].encode())
