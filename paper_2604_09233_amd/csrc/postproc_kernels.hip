@@ -113,10 +113,10 @@ __global__ __launch_bounds__(256) void dft_axis_kernel(const float2* __restrict_
 // axis) meet no bank conflict.  The direct sums above read LDS 2 n times per
 // output, which bounds them; these read it 2 (n1 + n2) times.  All reads of a
 // workgroup's columns come before its writes: in == out is allowed.
-// 96 x 96 x 48: a pass 14.9 -> 9.6 us (the middle two together 12.6), the call
-// 80 -> 47.5 us, error against 64 bits 5.6e-7 -> 2.6e-7; its 7 MB
-// take 1.5 us at the rate of a copy; the rest is the chain of load, two sums
-// and store, 2.3 workgroups per CU.  Loads before the twiddles
+// 96 x 96 x 48: the call 80 -> 45.5 us, error against 64 bits 5.7e-7 ->
+// 2.6e-7, a pass 14.9 -> 9.6 us (the middle two together 12.6; both at half
+// as many workgroups as now).  Its 7 MB take 1.5 us at the rate of a copy; the
+// rest is the chain of load, two sums and store.  Loads before the twiddles
 // rather than after them: 50.0 -> 47.5 us.
 // magic m of d: x / d = (x m) >> 32 for x < 2^16 (x m of 64 bits).
 __device__ __forceinline__ int div_magic(int x, unsigned m, int d) { return d == 1 ? x : (int)__umulhi((unsigned)x, m); }
@@ -282,7 +282,9 @@ hipError_t launch_dft_axis(const float2* in, float2* out, int64_t outer, int n, 
 }
 
 // Two factors nearest the root of n, and the columns of a workgroup: 16, fewer
-// until the pass has 512 workgroups, but at least one output per thread.
+// until the pass has 1024 workgroups (calls of 96x96x48 / 219x219x22 at 256,
+// 512, 1024 and 2048: 57.9, 47.3, 46.0, 49.8 / 242, 166, 144, 142 us), but at
+// least one output per thread.
 // The rule: they are taken where they save half the direct sum's terms and one column's outputs,
 // in turns of a workgroup's 256 threads, take no more terms than the direct
 // kernel's one output per thread (few columns and a long axis such as 3 x 677).
@@ -298,7 +300,7 @@ DftPlan dft_plan(int n, int64_t outer, int64_t inner) {
   auto blocks = [&] { return inner == 1 ? cdiv(outer, (int64_t)1 << p.lw) : outer * cdiv(inner, (int64_t)1 << p.lw); };
   auto slots = [&] { return n + 2 * (int64_t)n * ((1 << p.lw) | 1); };
   p.lw = 4;
-  while (p.lw > 0 && (slots() > 65536 / 8 || (blocks() < 512 && (n << p.lw) > 256))) --p.lw;
+  while (p.lw > 0 && (slots() > 65536 / 8 || (blocks() < 1024 && (n << p.lw) > 256))) --p.lw;
   auto magic = [](int d) { return (unsigned)((((uint64_t)1 << 32) + d - 1) / d); };  // d >= 2 where used
   p.m = magic(n);
   p.m1 = magic(p.n1);
