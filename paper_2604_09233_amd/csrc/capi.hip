@@ -1967,8 +1967,8 @@ extern "C" int nfs_encode_backward(nfs_ctx* ctx, const nfs_problem* prob, const 
   }
   if (grad_kcoef && y.K > 0 && y.P > 0 && precision == NFS_FP32) {
     NFS_TRY(launch_grad_kcoef_fused(y.grad, at<void>(ws, y.o_sB), at<void>(ws, y.o_vA), r, c.sens, prob->fields, G,
-                                    y.K, y.L, y.G, y.P, y.NQ, at<unsigned>(ws, y.o_tmax), at<float>(ws, y.o_bmax),
-                                    at<float>(ws, y.o_unscale), at<void>(ws, y.o_sA), grad_kcoef, c.s),
+                                    y.K, y.L, y.G, y.P, y.NQ, at<unsigned>(ws, y.o_tmax), at<void>(ws, y.o_sA), grad_kcoef,
+                                    c.s),
             "grad_kcoef_fused");
   } else if (grad_kcoef && y.K > 0 && y.P > 0) {
     // terms in groups through one E launch each, one by one past the groups

@@ -23,14 +23,26 @@ namespace nfs {
 // Operand layouts (per lane g = lane / 16, n = lane % 16, slots e = 0..7,
 // 16-byte vectors; part 0 = hi, 1 = lo; "kk" blocks of 16 coils):
 //  voxels   q  [(chunk * NK + kk) * 2 + part][64]: voxel 16 chunk + n, coil
-//           16 kk + 4 g + e / 2, re / im of S_c rho (e % 2), scaled;
+//           16 kk + 4 g + e / 2, re / im of S_c rho (e % 2), scaled per voxel;
 //  samples  Gf [(tile * NK + kk) * 2 + part][64]: sample 16 tile + n, same
 //           coils, (Gr, Gi), scaled per sample: the operand of Re D; that of
 //           Im D, (Gi, -Gr), is the same words with their halves turned;
 //  fields   hf [(pair * NP + np) * 2 + part][64]: term 16 np + n, voxel
-//           32 pair + 16 (e / 4) + 4 g + e % 4, scaled per term.
-// The scales are powers of two: |q| < 2^8 / (4 G) and |G| < 2^8 keep |w|
-// below 2^14 (|D| <= 2 G max|q| max|G|, |w| <= sqrt(2) |D|), |h| < 2.
+//           32 pair + 16 (e / 4) + 4 g + e % 4, times the voxel's scale,
+//           scaled per term.
+// Every scale is a power of two that puts the largest magnitude just below
+// 2^kTop.  The low f16 part ends at 2^-24, so values down to about 2^-16 of
+// that largest one keep all their 22 bits: of the coils of one voxel, of the
+// coils of one sample, and per term of h_b max_c |S_c rho|, which is what each
+// term's image had when every term went through E by itself.  (One scale for
+// the whole image and fields below 2 lost up to 10 bits of the high-order
+// terms of an object near the centre, and of everything beside one bright
+// voxel.)  w is scaled once more before its split: |D| <= 2 G 2^(2 kTop), so
+// |w| 2^-(kTop + ceil(log2 G)) <= 2^(kTop + 1), half of f16's largest value.
+// Sums over voxels stay below 2^(2 kTop + 1) L.
+constexpr int kTop = 14;
+constexpr int kNoExp = -(1 << 20);  // exponent of zero or of a value that is not finite
+
 __device__ __forceinline__ void store_split(const float (&v)[8], h8* out, int64_t block, int lane) {
   h8 hi, lo;
   split8(v, hi, lo);
@@ -38,47 +50,102 @@ __device__ __forceinline__ void store_split(const float (&v)[8], h8* out, int64_
   out[(block * 2 + 1) * 64 + lane] = lo;
 }
 
-__device__ __forceinline__ float pow2_below(float mx, int top) {  // largest 2^s with mx 2^s < 2^top
-  if (!(mx > 0.f) || !isfinite(mx)) return 1.f;
+__device__ __forceinline__ int top_exp(float mx) {  // mx < 2^top_exp
+  if (!(mx > 0.f) || !isfinite(mx)) return kNoExp;
   int e;
   frexpf(mx, &e);
+  return e;
+}
+
+__device__ __forceinline__ float pow2_below(float mx, int top) {  // largest 2^s with mx 2^s < 2^top
+  const int e = top_exp(mx);
+  if (e == kNoExp) return 1.f;
   const int s = top - e;
   return ldexpf(1.f, s > 100 ? 100 : (s < -100 ? -100 : s));
 }
 
+// largest |re|, |im| of S_c rho over the coils of voxel l
+__device__ __forceinline__ float voxel_max(const float2* __restrict__ rho, const float2* __restrict__ sens, int64_t l,
+                                           int64_t L, int G) {
+  const float2 r = rho[l];
+  float mx = 0.f;
+#pragma unroll 8
+  for (int c = 0; c < G; ++c) {
+    const float2 v = cmul(sens[(int64_t)c * L + l], r);
+    mx = fmaxf(mx, fmaxf(fabsf(v.x), fabsf(v.y)));
+  }
+  return mx;
+}
+
+// ve[l] = exponent of max_c |S_c rho|; em[b][x] = workgroup x's largest
+// exponent of |h_b| plus that of its voxel.  Maxima in registers, reduced once:
+// with an LDS atomic per voxel and term 36 us at 128x128, 16 coils, 16 terms.
+__global__ __launch_bounds__(256) void grad_range_kernel(const float2* __restrict__ rho,
+                                                         const float2* __restrict__ sens,
+                                                         const float* __restrict__ fields, int64_t L, int G, int P,
+                                                         int* __restrict__ ve, int* __restrict__ em) {
+  __shared__ int red[kWaves][kMaxTerms];
+  int mx[kMaxTerms];
+#pragma unroll
+  for (int b = 0; b < kMaxTerms; ++b) mx[b] = kNoExp;
+  for (int64_t l = (int64_t)blockIdx.x * 256 + threadIdx.x; l < L; l += (int64_t)gridDim.x * 256) {
+    const int e = top_exp(voxel_max(rho, sens, l, L, G));
+    ve[l] = e;
+#pragma unroll
+    for (int b = 0; b < kMaxTerms; ++b)
+      if (b < P) {
+        const int eh = top_exp(fabsf(fields[(int64_t)b * L + l]));
+        mx[b] = max(mx[b], e == kNoExp || eh == kNoExp ? kNoExp : e + eh);
+      }
+  }
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int b = 0; b < kMaxTerms; ++b)
+    if (b < P) {
+      for (int off = 32; off > 0; off >>= 1) mx[b] = max(mx[b], __shfl_xor(mx[b], off));
+      if (lane == 0) red[wave][b] = mx[b];
+    }
+  __syncthreads();
+  if ((int)threadIdx.x < P) {
+    int m = red[0][threadIdx.x];
+    for (int w = 1; w < kWaves; ++w) m = max(m, red[w][threadIdx.x]);
+    em[threadIdx.x * gridDim.x + blockIdx.x] = m;
+  }
+}
+
+// The voxels' operand; workgroup 0 also forms eb[b], the maximum of em[b].
 __global__ __launch_bounds__(256) void grad_pack_q_kernel(const float2* __restrict__ rho,
                                                           const float2* __restrict__ sens, int64_t L, int G, int NK,
-                                                          int64_t LC, const float* __restrict__ bmax, int top,
-                                                          float* __restrict__ unscale, h8* __restrict__ out) {
-  __shared__ float red[kBmaxBlocks];
-  red[threadIdx.x] = bmax[threadIdx.x];
-  __syncthreads();
-  for (int w = kBmaxBlocks / 2; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] = fmaxf(red[threadIdx.x], red[threadIdx.x + w]);
-    __syncthreads();
-  }
-  const float scale = pow2_below(red[0], top);
-  if (blockIdx.x == 0 && threadIdx.x == 0) *unscale = 1.f / scale;
+                                                          int64_t LC, const int* __restrict__ ve,
+                                                          const int* __restrict__ em, int nem, int P,
+                                                          int* __restrict__ eb, h8* __restrict__ out) {
+  if (blockIdx.x == 0)
+    for (int b = threadIdx.x >> 6; b < P; b += kWaves) {
+      int mx = kNoExp;
+      for (int x = threadIdx.x & 63; x < nem; x += 64) mx = max(mx, em[b * nem + x]);
+      for (int off = 32; off > 0; off >>= 1) mx = max(mx, __shfl_xor(mx, off));
+      if ((threadIdx.x & 63) == 0) eb[b] = mx;
+    }
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= LC * NK * 64) return;
   const int lane = (int)(i & 63), g = lane >> 4;
   const int64_t blk = i >> 6, l = blk / NK * kChunk + (lane & 15);
   const int kk = (int)(blk % NK);
+  const int e = l < L ? ve[l] : kNoExp, s = e == kNoExp ? 0 : kTop - e;
   float v[8];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int c = kk * 16 + g * 4 + j;
     float2 q = make_float2(0.f, 0.f);
     if (l < L && c < G) q = cmul(sens[(int64_t)c * L + l], rho[l]);
-    v[2 * j] = q.x * scale;
-    v[2 * j + 1] = q.y * scale;
+    v[2 * j] = ldexpf(q.x, s);
+    v[2 * j + 1] = ldexpf(q.y, s);
   }
   store_split(v, out, blk, lane);
 }
 
 __global__ __launch_bounds__(256) void grad_pack_G_kernel(const float2* __restrict__ gm, int64_t K, int G, int NK,
-                                                          int64_t KC, float* __restrict__ gunscale,
-                                                          h8* __restrict__ out) {
+                                                          int64_t KC, int* __restrict__ ge, h8* __restrict__ out) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= KC * NK * 64) return;
   const int lane = (int)(i & 63), g = lane >> 4;
@@ -90,38 +157,35 @@ __global__ __launch_bounds__(256) void grad_pack_G_kernel(const float2* __restri
       const float2 a = gm[(int64_t)c * K + k];
       mx = fmaxf(mx, fmaxf(fabsf(a.x), fabsf(a.y)));
     }
-  const float scale = pow2_below(mx, 8);
-  if (kk == 0 && g == 0) gunscale[k] = 1.f / scale;  // KC * 16 entries
-  float re[8];
+  const int e = top_exp(mx), s = e == kNoExp ? 0 : kTop - e;
+  if (kk == 0 && g == 0) ge[k] = e;  // KC * 16 entries
+  float v[8];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int c = kk * 16 + g * 4 + j;
     float2 a = make_float2(0.f, 0.f);
     if (k < K && c < G) a = gm[(int64_t)c * K + k];
-    re[2 * j] = a.x * scale;
-    re[2 * j + 1] = a.y * scale;
+    v[2 * j] = ldexpf(a.x, s);
+    v[2 * j + 1] = ldexpf(a.y, s);
   }
-  store_split(re, out, blk, lane);
-}
-
-// 2^-e_b with max|h_b| 2^-e_b in [1, 2)
-__device__ __forceinline__ float field_scale(const unsigned* tmax, int b) {
-  return pow2_below(__uint_as_float(tmax[kMaxTerms + b]), 1);
+  store_split(v, out, blk, lane);
 }
 
 __global__ __launch_bounds__(256) void grad_pack_h_kernel(const float* __restrict__ fields, int64_t L, int P, int NP,
-                                                          int64_t npair, const unsigned* __restrict__ tmax,
-                                                          h8* __restrict__ out) {
+                                                          int64_t npair, const int* __restrict__ ve,
+                                                          const int* __restrict__ eb, h8* __restrict__ out) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= npair * NP * 64) return;
   const int lane = (int)(i & 63), g = lane >> 4;
   const int64_t blk = i >> 6, pair = blk / NP;
   const int b = (int)(blk % NP) * 16 + (lane & 15);
+  const int top = b < P ? eb[b] : kNoExp;
   float v[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     const int64_t l = pair * 32 + (e >> 2) * 16 + g * 4 + (e & 3);
-    v[e] = b < P && l < L ? fields[(int64_t)b * L + l] * field_scale(tmax, b + 1) : 0.f;
+    const int s = l < L && top != kNoExp ? ve[l] : kNoExp;  // none: w is zero there, or nothing is finite
+    v[e] = s == kNoExp ? 0.f : ldexpf(fields[(int64_t)b * L + l], s + kTop - top);
   }
   store_split(v, out, blk, lane);
 }
@@ -130,7 +194,7 @@ __global__ __launch_bounds__(256) void grad_pack_h_kernel(const float* __restric
 // voxel chunks, staged through LDS and remapped to XCDs as in encode_kernel.
 template <int NQ, int NK, int NP, int MT, bool FRACT>
 __device__ __forceinline__ void grad_stream(const u4* __restrict__ strmcoef, const u4* __restrict__ q,
-                                            const u4* __restrict__ hf, int64_t p0, int64_t p1, int64_t LC,
+                                            const u4* __restrict__ hf, float wscale, int64_t p0, int64_t p1, int64_t LC,
                                             const u4 (&hc)[MT][NQ], const u4 (&gb)[MT][NK][2][2], f4 (&acc)[MT][NP],
                                             u4 (*stage)[(2 * NQ + 4 * NK + 2 * NP) * 64], int wave, int lane) {
   constexpr int kPh = 2 * NQ, kQ = 4 * NK, kBlk = kPh + kQ + 2 * NP;
@@ -184,7 +248,7 @@ __device__ __forceinline__ void grad_stream(const u4* __restrict__ strmcoef, con
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const float x = FRACT ? __builtin_amdgcn_fractf(p[r]) : p[r];
-          w[4 * u + r] = __builtin_amdgcn_cosf(x) * di[r] - __builtin_amdgcn_sinf(x) * dr[r];
+          w[4 * u + r] = (__builtin_amdgcn_cosf(x) * di[r] - __builtin_amdgcn_sinf(x) * dr[r]) * wscale;
         }
       }
       h8 wh, wl;
@@ -207,8 +271,9 @@ template <int NQ, int NK, int NP, int MT>
 __global__ __launch_bounds__(256) void grad_kcoef_fused_kernel(const u4* __restrict__ heldcoef,
                                                                const u4* __restrict__ strmcoef,
                                                                const u4* __restrict__ q, const u4* __restrict__ gf,
-                                                               const u4* __restrict__ hf, int64_t HC, int64_t LC,
-                                                               int64_t npair, int64_t pps, float* __restrict__ part,
+                                                               const u4* __restrict__ hf, float wscale, int64_t HC,
+                                                               int64_t LC, int64_t npair, int64_t pps,
+                                                               float* __restrict__ part,
                                                                const unsigned* __restrict__ tmax, int T) {
   __shared__ u4 stage[2][(2 * NQ + 4 * NK + 2 * NP) * 64];
   const int64_t b = xcd_order(blockIdx.x + (int64_t)gridDim.x * blockIdx.y, (int64_t)gridDim.x * gridDim.y);
@@ -235,8 +300,8 @@ __global__ __launch_bounds__(256) void grad_kcoef_fused_kernel(const u4* __restr
     for (int np = 0; np < NP; ++np) acc[mt][np] = f4{0.f, 0.f, 0.f, 0.f};
   }
   const int64_t p0 = split * pps, p1 = p0 + pps < npair ? p0 + pps : npair;
-  if (raw) grad_stream<NQ, NK, NP, MT, false>(strmcoef, q, hf, p0, p1, LC, hc, gb, acc, stage, wave, lane);
-  else grad_stream<NQ, NK, NP, MT, true>(strmcoef, q, hf, p0, p1, LC, hc, gb, acc, stage, wave, lane);
+  if (raw) grad_stream<NQ, NK, NP, MT, false>(strmcoef, q, hf, wscale, p0, p1, LC, hc, gb, acc, stage, wave, lane);
+  else grad_stream<NQ, NK, NP, MT, true>(strmcoef, q, hf, wscale, p0, p1, LC, hc, gb, acc, stage, wave, lane);
   const int g = lane >> 4, n = lane & 15;
   float* o = part + (size_t)split * (size_t)HC * 16 * (NP * 16);
 #pragma unroll
@@ -250,24 +315,26 @@ __global__ __launch_bounds__(256) void grad_kcoef_fused_kernel(const u4* __restr
   }
 }
 
-// out[k][b] = the split sums, unscaled
+// out[k][b] = the split sums, unscaled: 2^sh carries w's factor and the three
+// operands' kTop
 __global__ __launch_bounds__(256) void grad_kcoef_finish_kernel(const float* __restrict__ part, int nsplit,
-                                                                int64_t HC16, int NP, const float* __restrict__ unscale,
-                                                                const float* __restrict__ gunscale,
-                                                                const unsigned* __restrict__ tmax, int64_t K, int P,
-                                                                float* __restrict__ out) {
+                                                                int64_t HC16, int NP, int sh,
+                                                                const int* __restrict__ ge, const int* __restrict__ eb,
+                                                                int64_t K, int P, float* __restrict__ out) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= K * P) return;
   const int64_t k = i / P;
   const int b = (int)(i - k * P), ncol = NP * 16;
   float v = 0.f;
   for (int s = 0; s < nsplit; ++s) v += part[((size_t)s * HC16 + k) * ncol + b];
-  out[i] = v / field_scale(tmax, b + 1) * *unscale * gunscale[k];
+  out[i] = ldexpf(v, ge[k] + eb[b] + sh);
 }
 
 // ---------------------------------------------------------------------------
 static int grad_nk(int G) { return G <= 16 ? 1 : G <= 32 ? 2 : 4; }
 static int grad_np(int P) { return P <= 16 ? 1 : 2; }
+// workgroups of grad_range_kernel
+static int grad_range_blocks(int64_t L) { return (int)std::min<int64_t>(cdiv(L, 256), kBmaxBlocks); }
 // held tiles per wave: the samples' operands take 16 NK registers a tile
 static int grad_mt(int G) { return grad_nk(G) <= 2 ? 2 : 1; }
 
@@ -282,7 +349,10 @@ GradShape grad_shape(int64_t K, int64_t L, int G, int P, int n_cu, size_t avail)
   g.o_G = g.o_q + al((size_t)LC * g.NK * 2 * 1024);
   g.o_h = g.o_G + al((size_t)KC * g.NK * 2 * 1024);
   g.o_gs = g.o_h + al((size_t)g.npair * g.NP * 2 * 1024);
-  g.o_part = g.o_gs + al((size_t)KC * kChunk * 4);
+  g.o_ve = g.o_gs + al((size_t)KC * kChunk * 4);
+  g.o_eb = g.o_ve + al((size_t)L * 4);
+  g.o_em = g.o_eb + al(kMaxTerms * 4);
+  g.o_part = g.o_em + al((size_t)P * grad_range_blocks(L) * 4);
   const size_t one = (size_t)KC * kChunk * g.NP * 16 * 4;  // a multiple of 256
   // about four workgroups per CU, at least 8 pairs each, inside the space the
   // E^H E workspace has anyway
@@ -297,15 +367,15 @@ GradShape grad_shape(int64_t K, int64_t L, int G, int P, int n_cu, size_t avail)
 }
 
 template <int NQ>
-static hipError_t launch_fused_nq(const GradShape& g, int G, const u4* held, const u4* strm, const char* ws, int64_t KC,
-                                  int64_t LC, float* part, const unsigned* tmax, int T, hipStream_t s) {
+static hipError_t launch_fused_nq(const GradShape& g, int G, const u4* held, const u4* strm, const char* ws, float wscale,
+                                  int64_t KC, int64_t LC, float* part, const unsigned* tmax, int T, hipStream_t s) {
   const dim3 gr((unsigned)cdiv(KC, (int64_t)kWaves * grad_mt(G)), (unsigned)g.nsplit), bl(64 * kWaves);
   const u4 *q = (const u4*)(ws + g.o_q), *gf = (const u4*)(ws + g.o_G), *hf = (const u4*)(ws + g.o_h);
   switch (g.NK * 4 + g.NP) {
 #define NFS_GRAD(nk, np, mt)                                                                                       \
   case nk * 4 + np:                                                                                                \
-    hipLaunchKernelGGL((grad_kcoef_fused_kernel<NQ, nk, np, mt>), gr, bl, 0, s, held, strm, q, gf, hf, KC, LC, g.npair, \
-                       g.pps, part, tmax, T);                                                                       \
+    hipLaunchKernelGGL((grad_kcoef_fused_kernel<NQ, nk, np, mt>), gr, bl, 0, s, held, strm, q, gf, hf, wscale, KC, LC, \
+                       g.npair, g.pps, part, tmax, T);                                                              \
     break;
     NFS_GRAD(1, 1, 2)
     NFS_GRAD(1, 2, 2)
@@ -321,33 +391,36 @@ static hipError_t launch_fused_nq(const GradShape& g, int G, const u4* held, con
 
 hipError_t launch_grad_kcoef_fused(const GradShape& g, const void* heldcoef, const void* strmcoef, const float2* rho,
                                    const float2* sens, const float* fields, const float2* grad_m, int64_t K, int64_t L,
-                                   int G, int P, int NQ, const unsigned* tmax, float* bmax, float* unscale, void* ws,
-                                   float* out, hipStream_t s) {
+                                   int G, int P, int NQ, const unsigned* tmax, void* ws, float* out, hipStream_t s) {
   if (K == 0 || P == 0) return hipSuccess;
   if (L == 0) return launch_fill_zero(out, K * P, s);
   const int64_t KC = cdiv(K, kChunk), LC = cdiv(L, kChunk);
   char* w = (char*)ws;
-  hipError_t e = launch_absmax(rho, sens, nullptr, L, 1, 0, G, bmax, nullptr, s);
-  if (e != hipSuccess) return e;
   int lg = 0;
-  while ((1 << lg) < 4 * G) ++lg;
+  while ((1 << lg) < G) ++lg;
+  const int wsh = kTop + lg;
+  const float wscale = ldexpf(1.f, -wsh);
+  int *ve = (int*)(w + g.o_ve), *em = (int*)(w + g.o_em), *eb = (int*)(w + g.o_eb), *ge = (int*)(w + g.o_gs);
+  const int nem = grad_range_blocks(L);
   auto blocks = [](int64_t n) { return dim3((unsigned)cdiv(n, 256)); };
-  hipLaunchKernelGGL(grad_pack_q_kernel, blocks(LC * g.NK * 64), dim3(256), 0, s, rho, sens, L, G, g.NK, LC, bmax,
-                     14 - 8 - lg + 2, unscale, (h8*)(w + g.o_q));
-  hipLaunchKernelGGL(grad_pack_G_kernel, blocks(KC * g.NK * 64), dim3(256), 0, s, grad_m, K, G, g.NK, KC,
-                     (float*)(w + g.o_gs), (h8*)(w + g.o_G));
-  hipLaunchKernelGGL(grad_pack_h_kernel, blocks(g.npair * g.NP * 64), dim3(256), 0, s, fields, L, P, g.NP, g.npair,
-                     tmax, (h8*)(w + g.o_h));
-  if ((e = hipGetLastError()) != hipSuccess) return e;
+  hipLaunchKernelGGL(grad_range_kernel, dim3(nem), dim3(256), 0, s, rho, sens, fields, L, G, P, ve, em);
+  hipLaunchKernelGGL(grad_pack_q_kernel, blocks(LC * g.NK * 64), dim3(256), 0, s, rho, sens, L, G, g.NK, LC, ve, em,
+                     nem, P, eb, (h8*)(w + g.o_q));
+  hipLaunchKernelGGL(grad_pack_G_kernel, blocks(KC * g.NK * 64), dim3(256), 0, s, grad_m, K, G, g.NK, KC, ge,
+                     (h8*)(w + g.o_G));
+  hipLaunchKernelGGL(grad_pack_h_kernel, blocks(g.npair * g.NP * 64), dim3(256), 0, s, fields, L, P, g.NP, g.npair, ve,
+                     eb, (h8*)(w + g.o_h));
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
   float* part = (float*)(w + g.o_part);
   const u4 *held = (const u4*)heldcoef, *strm = (const u4*)strmcoef;
-  e = NQ == 1   ? launch_fused_nq<1>(g, G, held, strm, w, KC, LC, part, tmax, P + 1, s)
-      : NQ == 2 ? launch_fused_nq<2>(g, G, held, strm, w, KC, LC, part, tmax, P + 1, s)
-      : NQ == 3 ? launch_fused_nq<3>(g, G, held, strm, w, KC, LC, part, tmax, P + 1, s)
+  e = NQ == 1   ? launch_fused_nq<1>(g, G, held, strm, w, wscale, KC, LC, part, tmax, P + 1, s)
+      : NQ == 2 ? launch_fused_nq<2>(g, G, held, strm, w, wscale, KC, LC, part, tmax, P + 1, s)
+      : NQ == 3 ? launch_fused_nq<3>(g, G, held, strm, w, wscale, KC, LC, part, tmax, P + 1, s)
                 : hipErrorInvalidValue;
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(grad_kcoef_finish_kernel, blocks(K * P), dim3(256), 0, s, part, g.nsplit, KC * kChunk, g.NP,
-                     unscale, (const float*)(w + g.o_gs), tmax, K, P, out);
+                     wsh - 3 * kTop, ge, eb, K, P, out);
   return hipGetLastError();
 }
 
@@ -367,12 +440,7 @@ __global__ __launch_bounds__(256) void grad_terms_absmax_kernel(const float2* __
   if (threadIdx.x < kMaxTerms) red[threadIdx.x] = 0u;
   __syncthreads();
   for (int64_t l = (int64_t)blockIdx.x * 256 + threadIdx.x; l < L; l += (int64_t)gridDim.x * 256) {
-    float mx = 0.f;
-    const float2 r = rho[l];
-    for (int c = 0; c < G; ++c) {
-      const float2 v = cmul(sens[(int64_t)c * L + l], r);
-      mx = fmaxf(mx, fmaxf(fabsf(v.x), fabsf(v.y)));
-    }
+    const float mx = voxel_max(rho, sens, l, L, G);
     for (int b = 0; b < P; ++b) {
       const float v = fabsf(fields[(int64_t)b * L + l]) * mx;
       if (v > 0.f) atomicMax(&red[b], __float_as_uint(v));

@@ -210,7 +210,7 @@ hipError_t launch_grad_kcoef(const float* epart, int nsplit, int64_t HC16, int N
 struct GradShape {
   int NK, NP, nsplit;
   int64_t npair, pps;
-  size_t o_q, o_G, o_h, o_gs, o_part, total;
+  size_t o_q, o_G, o_h, o_gs, o_ve, o_eb, o_em, o_part, total;
 };
 // as many splits as fit into `avail` bytes (at least one)
 GradShape grad_shape(int64_t K, int64_t L, int G, int P, int n_cu, size_t avail);
@@ -218,8 +218,7 @@ GradShape grad_shape(int64_t K, int64_t L, int G, int P, int n_cu, size_t avail)
 // samples (role B) and voxels (role A); ws: grad_shape().total bytes
 hipError_t launch_grad_kcoef_fused(const GradShape& g, const void* heldcoef, const void* strmcoef, const float2* rho,
                                    const float2* sens, const float* fields, const float2* grad_m, int64_t K, int64_t L,
-                                   int G, int P, int NQ, const unsigned* tmax, float* bmax, float* unscale, void* ws,
-                                   float* out, hipStream_t s);
+                                   int G, int P, int NQ, const unsigned* tmax, void* ws, float* out, hipStream_t s);
 
 // Several terms per E launch (FP16, BF16): group size n (1: not offered), column
 // blocks, held tiles and splits of its E launches, offsets in a buffer of

@@ -1,0 +1,86 @@
+"""The FP32 gradient of the field coefficients on operands of very different
+size, judged term by term (or sample by sample) against the FP64 formula: a
+small object near the centre, where high-order terms are small; one voxel far
+brighter than the rest where the terms vanish; coils of very different scale;
+magnitudes near both ends of float32.  Three operand splits of 2^-22 and the
+phase's 2^-21 of its bound (30 rad here: 1.4e-5 rad at most) give a few 1e-6; 3e-5 holds
+where only the operands' scales differ."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+
+pytestmark = pytest.mark.gpu
+BAR = 3e-5
+
+
+def run(d, g):
+    from paper_2604_09233_amd import nfs
+
+    gp = nfs.Problem(d["sens"], d["fields"], d["b0"], d["kcoef"], d["t"])
+    gk = nfs.encode_backward(gp, torch.from_numpy(d["rho"]), torch.from_numpy(g), "fp32", False, False, True)[2]
+    got = gk.cpu().numpy().astype(np.float64)
+    a = (d["sens"].astype(np.complex128), d["fields"], d["b0"], d["kcoef"], d["t"])
+    ref = np.empty_like(got)
+    for b in range(ref.shape[1]):
+        z = oracle.apply_E(d["fields"][b].astype(np.float64) * d["rho"].astype(np.complex128), *a)
+        ref[:, b] = np.imag(np.sum(g.astype(np.complex128) * np.conj(z), axis=0))
+    return got, ref
+
+
+def per_term(got, ref):
+    return np.linalg.norm(got - ref, axis=0) / np.linalg.norm(ref, axis=0)
+
+
+@pytest.mark.parametrize("G", [3, 16, 32, 64])
+@pytest.mark.parametrize("radius", [0.1, 0.02])
+def test_small_object(radius, G):
+    """The object inside a fraction of the half-width: its third-order terms
+    are radius^3 of the largest field value."""
+    n = 48
+    y, x = np.mgrid[:n, :n].reshape(2, -1) / (n / 2.0) - 1.0 + 0.5 / n
+    z = np.full_like(x, 0.4 * radius)
+    f = [x, y, x * y, x * x - y * y, 3 * x * x * y - y ** 3, x ** 3 - 3 * x * y * y, x * y * z, z * (x * x - y * y)]
+    d = synth.random_problem(n * n, 200, G, len(f), seed=95, phase_scale=10.0)
+    d["fields"] = np.stack(f).astype(np.float32)
+    near = np.argsort(x * x + y * y)[:max(6, int((radius * n / 2) ** 2 * np.pi))]
+    rho = np.zeros(n * n, np.complex64)
+    rho[near] = d["rho"][near]
+    d["rho"] = rho
+    e = per_term(*run(d, d["m"]))
+    print(f"radius {radius} G={G}: worst term {e.max():.1e}")
+    assert e.max() < BAR
+
+
+@pytest.mark.parametrize("G", [16, 32, 64])
+@pytest.mark.parametrize("bright", [1e4, 1e6])
+def test_bright_voxel_where_the_terms_vanish(bright, G):
+    d = synth.random_problem(700, 200, G, 5, seed=96, phase_scale=10.0)
+    d["rho"][333] *= bright
+    d["fields"][:, 333] = 0
+    e = per_term(*run(d, d["m"]))
+    print(f"bright voxel {bright:.0e} G={G}: worst term {e.max():.1e}")
+    assert e.max() < BAR
+
+
+@pytest.mark.parametrize("G", [16, 64])
+def test_coils_of_different_scale(G):
+    d = synth.random_problem(500, 200, G, 5, seed=97, phase_scale=10.0)
+    s = np.logspace(-2, 2, G).astype(np.float32)
+    d["sens"] = d["sens"] * s[:, None]
+    e = per_term(*run(d, d["m"] / s[:, None]))
+    print(f"coil scales 1e-2 to 1e2, G={G}: worst term {e.max():.1e}")
+    assert e.max() < BAR
+
+
+@pytest.mark.parametrize("rho,grad,field", [(1, 1e-35, 1), (1, 1e34, 1), (1e-6, 1e36, 1e-6), (1e12, 1e-37, 1e3)])
+def test_magnitudes(rho, grad, field):
+    d = synth.random_problem(300, 100, 4, 3, seed=98, phase_scale=10.0)
+    d["rho"] = d["rho"] * np.float32(rho)
+    d["fields"] = d["fields"] * np.float32(field)
+    d["kcoef"] = d["kcoef"] / np.float32(field)
+    e = per_term(*run(d, d["m"] * np.float32(grad)))
+    print(f"rho {rho:.0e} grad {grad:.0e} field {field:.0e}: worst term {e.max():.1e}")
+    assert e.max() < BAR
