@@ -42,6 +42,7 @@ namespace nfs {
 // Sums over voxels stay below 2^(2 kTop + 1) L.
 constexpr int kTop = 14;
 constexpr int kNoExp = -(1 << 20);  // exponent of zero or of a value that is not finite
+constexpr int kInfExp = 1 << 20;    // of a sample with an infinite gradient
 
 __device__ __forceinline__ void store_split(const float (&v)[8], h8* out, int64_t block, int lane) {
   h8 hi, lo;
@@ -157,7 +158,14 @@ __global__ __launch_bounds__(256) void grad_pack_G_kernel(const float2* __restri
       const float2 a = gm[(int64_t)c * K + k];
       mx = fmaxf(mx, fmaxf(fabsf(a.x), fabsf(a.y)));
     }
-  const int e = top_exp(mx), s = e == kNoExp ? 0 : kTop - e;
+  // beside an infinite entry finite ones count for nothing: its sign goes
+  // through (a split of infinity itself is not a number), the size is put back
+  // at the end
+  const bool inf = isinf(mx);
+  const int e = inf ? kInfExp : top_exp(mx), s = inf || e == kNoExp ? 0 : kTop - e;
+  auto entry = [&](float x) {
+    return !inf || isnan(x) ? ldexpf(x, s) : isinf(x) ? copysignf(ldexpf(1.f, kTop - 1), x) : 0.f;
+  };
   if (kk == 0 && g == 0) ge[k] = e;  // KC * 16 entries
   float v[8];
 #pragma unroll
@@ -165,8 +173,8 @@ __global__ __launch_bounds__(256) void grad_pack_G_kernel(const float2* __restri
     const int c = kk * 16 + g * 4 + j;
     float2 a = make_float2(0.f, 0.f);
     if (k < K && c < G) a = gm[(int64_t)c * K + k];
-    v[2 * j] = ldexpf(a.x, s);
-    v[2 * j + 1] = ldexpf(a.y, s);
+    v[2 * j] = entry(a.x);
+    v[2 * j + 1] = entry(a.y);
   }
   store_split(v, out, blk, lane);
 }
@@ -327,7 +335,7 @@ __global__ __launch_bounds__(256) void grad_kcoef_finish_kernel(const float* __r
   const int b = (int)(i - k * P), ncol = NP * 16;
   float v = 0.f;
   for (int s = 0; s < nsplit; ++s) v += part[((size_t)s * HC16 + k) * ncol + b];
-  out[i] = ldexpf(v, ge[k] + eb[b] + sh);
+  out[i] = ge[k] == kInfExp ? v * INFINITY : ldexpf(v, ge[k] + eb[b] + sh);
 }
 
 // ---------------------------------------------------------------------------

@@ -84,3 +84,26 @@ def test_magnitudes(rho, grad, field):
     e = per_term(*run(d, d["m"] * np.float32(grad)))
     print(f"rho {rho:.0e} grad {grad:.0e} field {field:.0e}: worst term {e.max():.1e}")
     assert e.max() < BAR
+
+
+@pytest.mark.parametrize("part", [1, 1j])
+@pytest.mark.parametrize("G", [1, 5, 33])
+def test_infinite_and_nan_gradients_stay_in_their_samples(G, part):
+    """An infinite entry gives its sample infinite derivatives of the sign of
+    its own product, NaN gives NaN, and every other sample keeps its bits."""
+    d = synth.random_problem(300, 100, G, 3, seed=99, phase_scale=10.0)
+    g = d["m"].copy()
+    clean, _ = run(d, g)
+    only = np.zeros_like(g)
+    for k, v in ((7, np.inf), (16, -np.inf)):
+        re_im = g.view(np.float32).reshape(G, -1, 2)
+        re_im[G - 1, k, 0 if part == 1 else 1] = v
+        only[G - 1, k] = np.sign(v) * part
+    g[0, 50] = np.nan
+    sign = run(d, only)[1]
+    got, _ = run(d, g)
+    for k in (7, 16):
+        assert np.array_equal(got[k], np.sign(sign[k]) * np.inf)
+    assert np.isnan(got[50]).all()
+    rest = np.setdiff1d(np.arange(100), [7, 16, 50])
+    assert np.array_equal(got[rest], clean[rest])
