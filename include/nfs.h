@@ -112,6 +112,12 @@ int nfs_destroy(nfs_ctx* ctx);
  * also depends on n_iter and reorth (both ignored for the other ops);
  * NFS_OP_CG_RESIDENT (nfs_cg_solve_resident) adds 2 K L x 4 bytes for the
  * resident P and takes only NFS_FP16 (NFS_EUNSUPPORTED otherwise).
+ * For the operators (NFS_OP_E, NFS_OP_EH, NFS_OP_EHE) this is the size at which they
+ * are fastest, with split partials of their own, up to about 220 MB more
+ * than they need; it may exceed NFS_OP_CG's.  They also run, with fewer splits
+ * (other last bits), in less: a workspace of NFS_OP_CG bytes for the same
+ * problem and precision holds each of them and nfs_encode_backward.  Below the
+ * solves' split counts they return NFS_EWORKSPACE.
  * Host-only; never touches the device.                                    */
 int nfs_workspace_bytes(const nfs_ctx* ctx, const nfs_problem* prob, int op, int precision,
                         int n_iter, int reorth, size_t* bytes);

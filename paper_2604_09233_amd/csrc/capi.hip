@@ -292,8 +292,9 @@ static int operator_split(int op, int64_t held_chunks, int64_t strm_chunks, int 
 // Encode shape of one direction: held-tile count MT and split count, from
 // (in order) an explicit override, the context's autotuned entry, or the
 // defaults for the call `call` (an nfs_op).  Held tiles do not change results.
+// cap: bound on an operator's default split count, as far as the solves' count.
 static EncodeShape encode_shape(const nfs_ctx* ctx, const nfs_problem* pr, int op, int prec, int NQ, int NB,
-                                int64_t HC, int64_t SC, const int* ov, int call = NFS_OP_CG) {
+                                int64_t HC, int64_t SC, const int* ov, int call = NFS_OP_CG, int cap = 64) {
   const int n_cu = ctx ? ctx->n_cu : 256;
   int MT = 0, ns = 0;
   if (ov) {
@@ -309,7 +310,8 @@ static EncodeShape encode_shape(const nfs_ctx* ctx, const nfs_problem* pr, int o
   if (ns < 1) {
     const int big = valid_held_tiles(NB, 4) ? 4 : 2;
     const bool solve = call == NFS_OP_CG || call == NFS_OP_CG_RESIDENT;
-    ns = solve ? solve_split(HC, SC, NB, n_cu) : operator_split(op, HC, SC, NB, big, n_cu, call != NFS_OP_EHE);
+    ns = solve_split(HC, SC, NB, n_cu);
+    if (!solve) ns = std::max(ns, std::min(cap, operator_split(op, HC, SC, NB, big, n_cu, call != NFS_OP_EHE)));
     // Four held tiles read each staged chunk half as often as two, but a
     // last round of workgroups that leaves most CUs idle lasts twice as long.
     // So four from two workgroups per CU on (48x48x24, 32 coils: E 648 -> 590
@@ -331,7 +333,10 @@ static EncodeShape encode_shape(const nfs_ctx* ctx, const nfs_problem* pr, int o
   return sh;
 }
 
-static Layout make_layout(const nfs_ctx* ctx, const nfs_problem* pr, int op, int prec, int n_iter, int reorth) {
+// capE, capH: bounds on the default split counts of operators; limit: bytes
+// within which the one-pass grad_kcoef has to fit to be offered (nsplit > 0).
+static Layout make_layout(const nfs_ctx* ctx, const nfs_problem* pr, int op, int prec, int n_iter, int reorth,
+                          int capE = 64, int capH = 64, size_t limit = SIZE_MAX) {
   Layout y{};
   y.L = pr->n_vox;
   y.K = pr->n_samp;
@@ -343,8 +348,8 @@ static Layout make_layout(const nfs_ctx* ctx, const nfs_problem* pr, int op, int
   y.NB = col_blocks(y.G);
   y.prec = prec;
   const bool cg = op == NFS_OP_CG || op == NFS_OP_CG_RESIDENT;
-  y.shE = encode_shape(ctx, pr, OP_E, prec, y.NQ, y.NB, y.KC, y.LC, nullptr, op);
-  y.shH = encode_shape(ctx, pr, OP_EH, prec, y.NQ, y.NB, y.LC, y.KC, nullptr, op);
+  y.shE = encode_shape(ctx, pr, OP_E, prec, y.NQ, y.NB, y.KC, y.LC, nullptr, op, capE);
+  y.shH = encode_shape(ctx, pr, OP_EH, prec, y.NQ, y.NB, y.LC, y.KC, nullptr, op, capH);
   const bool needE = op != NFS_OP_EH, needH = op != NFS_OP_E;
 
   size_t o = 0;
@@ -392,9 +397,33 @@ static Layout make_layout(const nfs_ctx* ctx, const nfs_problem* pr, int op, int
   y.o_hpart = needH ? take(hpart_bytes(y.shH)) : 0;
   if (op == NFS_OP_EHE && prec == PREC_FP32 && y.P > 0) {
     y.grad = grad_shape(y.K, y.L, y.G, y.P, ctx ? ctx->n_cu : 256, o - y.o_sA);
-    o = std::max(o, y.o_sA + y.grad.total);  // larger only for a few chunks with over 16 terms
+    if (y.o_sA + y.grad.total <= std::max(o, limit)) o = std::max(o, y.o_sA + y.grad.total);  // larger for a few chunks
+    else y.grad.nsplit = 0;
   }
   y.total = o;
+  return y;
+}
+
+// Layout of an operator call in a workspace of `bytes`.  Everything past the
+// solves' split counts is for speed alone, so where the size asked for is not
+// there (a caller's solve workspace, which held every operator before they
+// had split counts of their own) E takes fewer splits, then E^H, down to the
+// solves' counts, and grad_kcoef goes term by term.  16384 voxels, 60 000
+// samples, 16 coils, FP16, in a solve's workspace (70 MB): E 344 us, E^H E 617;
+// in their own (127 and 149 MB) 322 and 610.
+static Layout operator_layout(const nfs_ctx* ctx, const nfs_problem* pr, int op, int prec, size_t bytes) {
+  Layout y = make_layout(ctx, pr, op, prec, 0, 0);
+  if (y.total <= bytes) return y;
+  int capE = y.shE.nsplit, capH = y.shH.nsplit;
+  auto again = [&] { y = make_layout(ctx, pr, op, prec, 0, 0, capE, capH, bytes); };
+  auto lower = [&](int& cap, size_t one) {  // `one`: bytes of one split's partials
+    if (y.total <= bytes || one == 0) return;
+    cap -= (int)std::min<int64_t>(cap - 1, cdiv((int64_t)(y.total - bytes), (int64_t)one));
+    again();
+  };
+  again();
+  lower(capE, op != NFS_OP_EH ? epart_bytes(y.shE, y.NB) / y.shE.nsplit : 0);
+  lower(capH, op != NFS_OP_E ? hpart_bytes(y.shH) / y.shH.nsplit : 0);
   return y;
 }
 
@@ -615,7 +644,7 @@ extern "C" int nfs_apply_E(nfs_ctx* ctx, const nfs_problem* prob, const float* r
   if ((rc = check_prec(precision, fn))) return rc;
   if ((rc = check_vec(rho, prob->n_vox, fn, "rho"))) return rc;
   if ((rc = check_vec(m, prob->n_samp, fn, "m"))) return rc;
-  const Layout y = make_layout(ctx, prob, NFS_OP_E, precision, 0, 0);
+  const Layout y = operator_layout(ctx, prob, NFS_OP_E, precision, ws_bytes);
   if ((rc = check_ws(y, ws, ws_bytes, fn))) return rc;
   if (y.K == 0) return NFS_OK;
   Ctx c{ctx, y, prob, reinterpret_cast<const float2*>(prob->sens), ws, (hipStream_t)stream, nullptr};
@@ -636,7 +665,7 @@ extern "C" int nfs_apply_EH(nfs_ctx* ctx, const nfs_problem* prob, const float* 
   if ((rc = check_prec(precision, fn))) return rc;
   if ((rc = check_vec(m, prob->n_samp, fn, "m"))) return rc;
   if ((rc = check_vec(x, prob->n_vox, fn, "x"))) return rc;
-  const Layout y = make_layout(ctx, prob, NFS_OP_EH, precision, 0, 0);
+  const Layout y = operator_layout(ctx, prob, NFS_OP_EH, precision, ws_bytes);
   if ((rc = check_ws(y, ws, ws_bytes, fn))) return rc;
   if (y.L == 0) return NFS_OK;
   Ctx c{ctx, y, prob, reinterpret_cast<const float2*>(prob->sens), ws, (hipStream_t)stream, nullptr};
@@ -657,7 +686,7 @@ extern "C" int nfs_apply_EHE(nfs_ctx* ctx, const nfs_problem* prob, const float*
   if ((rc = check_prec(precision, fn))) return rc;
   if ((rc = check_vec(p, prob->n_vox, fn, "p"))) return rc;
   if ((rc = check_vec(q, prob->n_vox, fn, "q"))) return rc;
-  const Layout y = make_layout(ctx, prob, NFS_OP_EHE, precision, 0, 0);
+  const Layout y = operator_layout(ctx, prob, NFS_OP_EHE, precision, ws_bytes);
   if ((rc = check_ws(y, ws, ws_bytes, fn))) return rc;
   if (y.L == 0) return NFS_OK;
   Ctx c{ctx, y, prob, reinterpret_cast<const float2*>(prob->sens), ws, (hipStream_t)stream, nullptr};
@@ -1947,7 +1976,7 @@ extern "C" int nfs_encode_backward(nfs_ctx* ctx, const nfs_problem* prob, const 
   if ((rc = check_vec(grad_rho, 0, fn, "grad_rho"))) return rc;
   if (misaligned(grad_b0, 4) || misaligned(grad_kcoef, 4))
     return fail(NFS_EINVAL, "%s: gradient array not 4-byte aligned", fn);
-  const Layout y = make_layout(ctx, prob, NFS_OP_EHE, precision, 0, 0);
+  const Layout y = operator_layout(ctx, prob, NFS_OP_EHE, precision, ws_bytes);
   if ((rc = check_ws(y, ws, ws_bytes, fn))) return rc;
   Ctx c{ctx, y, prob, reinterpret_cast<const float2*>(prob->sens), ws, (hipStream_t)stream, nullptr};
   const float2* G = reinterpret_cast<const float2*>(grad_m);
@@ -1965,7 +1994,7 @@ extern "C" int nfs_encode_backward(nfs_ctx* ctx, const nfs_problem* prob, const 
                            c.s),
             "grad_b0");
   }
-  if (grad_kcoef && y.K > 0 && y.P > 0 && precision == NFS_FP32) {
+  if (grad_kcoef && y.K > 0 && y.P > 0 && precision == NFS_FP32 && (y.grad.nsplit > 0 || y.L == 0)) {
     NFS_TRY(launch_grad_kcoef_fused(y.grad, at<void>(ws, y.o_sB), at<void>(ws, y.o_vA), r, c.sens, prob->fields, G,
                                     y.K, y.L, y.G, y.P, y.NQ, at<unsigned>(ws, y.o_tmax), at<void>(ws, y.o_sA), grad_kcoef,
                                     c.s),
@@ -1973,7 +2002,8 @@ extern "C" int nfs_encode_backward(nfs_ctx* ctx, const nfs_problem* prob, const 
   } else if (grad_kcoef && y.K > 0 && y.P > 0) {
     // terms in groups through one E launch each, one by one past the groups
     char* g = at<char>(ws, y.o_sA);
-    const GradTerms gt = y.L > 0 ? grad_terms(y.prec, y.KC, y.LC, y.G, y.P, y.shE.nsplit, ctx->n_cu, y.total - y.o_sA)
+    const bool grouped = y.L > 0 && precision != NFS_FP32;
+    const GradTerms gt = grouped ? grad_terms(y.prec, y.KC, y.LC, y.G, y.P, y.shE.nsplit, ctx->n_cu, y.total - y.o_sA)
                                  : GradTerms{1};
     int b = 0;
     if (gt.n > 1) {
