@@ -406,7 +406,8 @@ int nfs_autotune_batched(nfs_ctx* ctx, int n_slices, const nfs_problem* probs, i
 /* The encode shape later solves will use for `op` (NFS_OP_E or NFS_OP_EH):
  * held tiles per wave and split count (tuned, else the default choice).
  * Single operator calls use the same shape when it is tuned or pinned and a
- * default of their own (more splits) when it is not.                       */
+ * default of their own (more splits) when it is not; a batch's slices then
+ * hold tiles by a rule of the batch (same splits, same results).           */
 int nfs_tuned_shape(const nfs_ctx* ctx, const nfs_problem* prob, int precision, int op, int* held_tiles,
                     int* nsplit);
 /* Pin the encode shape of `op` (NFS_OP_E or NFS_OP_EH) for this problem's

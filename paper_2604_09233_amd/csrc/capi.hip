@@ -1627,6 +1627,27 @@ static bool lockstep_ok(int n, const std::vector<Layout>& ys) {
   return true;
 }
 
+// Held tiles of a batch's untuned slices (they do not change results).  The
+// rule of a launch by itself (encode_shape) does not fit here: other slices
+// fill the CUs that the last workgroups of one leave idle, and in the lock-step
+// form slices of one coil class share a work list only with equal held tiles.
+// So four wherever built, for slices on streams from two workgroups per CU on.
+// 16 terms, 5 iterations, ms, two tiles / the single launch's rule / four:
+// lock-step, 20 slices, 9 to 16 coils, 96x96 to 160x160, BF16 28.5 / 26.6 /
+// 25.5; 10 slices, 2 to 32 coils, 64x64 to 200x200, BF16 20.3 / 19.2 / 18.5,
+// FP16 15.5 / 15.2 / 14.4; 16 slices, 17 to 32 coils, 48x48 to 96x96, FP16 7.9 /
+// 7.8 / 8.0; on streams, the 20 slices 26.6 / 25.5 / 24.1, the 10 FP16 14.3 /
+// 14.3 / 13.6; 16 slices, 9 to 16 coils, 40x40 to 80x80, FP16 4.8 / 4.7 / 5.0.
+static void batch_held_tiles(const nfs_ctx* ctx, const nfs_problem* probs, std::vector<Layout>& ys, bool lockstep) {
+  if (ys.size() < 2) return;
+  for (size_t i = 0; i < ys.size(); ++i)
+    for (EncodeShape* sh : {&ys[i].shE, &ys[i].shH}) {
+      if (ctx->tune.count(tune_key(sh->op, sh->prec, &probs[i]))) continue;
+      const int big = valid_held_tiles(sh->NB, 4) ? 4 : 2;
+      sh->MT = lockstep || cdiv(sh->HC, (int64_t)kWaves * big) * sh->nsplit >= 2LL * ctx->n_cu ? big : 2;
+    }
+}
+
 // The persistent encode launches of one direction (op OP_E or OP_EH) over
 // all slices: one launch per shape class (phase instructions, column
 // blocks, held tiles), at most kMaxBatchItems slices each.  The classes are
@@ -1938,6 +1959,7 @@ extern "C" int nfs_cg_solve_batched(nfs_ctx* ctx, int n_slices, const nfs_proble
     ptrs.push_back(info ? info[i] : nullptr);
   }
   const bool lockstep = ctx->batch_mode == NFS_BATCH_PERSISTENT && lockstep_ok(n_slices, ys);
+  batch_held_tiles(ctx, probs, ys, lockstep);
   const std::string key = graph_key(ctx, lockstep ? "cgbp" : "cgb", probs, n_slices, ptrs.data(), (int)ptrs.size(),
                                     n_iter, tol, replace_every, reorth, precision, ws, ws_bytes, stream);
   if (lockstep)
