@@ -395,7 +395,12 @@ static Layout make_layout(const nfs_ctx* ctx, const nfs_problem* pr, int op, int
   // split partials last: their sizes depend on the encode shapes
   y.o_epart = needE ? take(epart_bytes(y.shE, y.NB)) : 0;
   y.o_hpart = needH ? take(hpart_bytes(y.shH)) : 0;
-  if (op == NFS_OP_EHE && prec == PREC_FP32 && y.P > 0) {
+  // One pass for grad_kcoef from two terms on; a single one is one E, which up
+  // to 16 coils is less work per pair than the pass (FP32, E / one pass, us:
+  // 16384 voxels, 60 000 samples, 8 coils 354 / 534, 16 coils 488 / 569; 4000
+  // and 4000, 16 coils 40 / 45; 10 000 and 20 000, 33 coils 324 / 305; two
+  // terms, 16384 and 60 000, 8 coils 696 / 540).
+  if (op == NFS_OP_EHE && prec == PREC_FP32 && (y.P > 1 || (y.P == 1 && y.NB > 2))) {
     y.grad = grad_shape(y.K, y.L, y.G, y.P, ctx ? ctx->n_cu : 256, o - y.o_sA);
     if (y.o_sA + y.grad.total <= std::max(o, limit)) o = std::max(o, y.o_sA + y.grad.total);  // larger for a few chunks
     else y.grad.nsplit = 0;

@@ -107,3 +107,21 @@ def test_infinite_and_nan_gradients_stay_in_their_samples(G, part):
     assert np.isnan(got[50]).all()
     rest = np.setdiff1d(np.arange(100), [7, 16, 50])
     assert np.array_equal(got[rest], clean[rest])
+
+
+@pytest.mark.parametrize("G,P,encodes", [(1, 1, 1), (16, 1, 1), (17, 1, 0), (16, 2, 0)])
+def test_one_term_is_one_encode(G, P, encodes):
+    """A single term up to 16 coils takes one E instead of the one pass."""
+    from paper_2604_09233_amd import nfs
+
+    d = synth.random_problem(700, 400, G, P, seed=94, phase_scale=10.0)
+    nfs.profile_enable(0, True)
+    try:
+        nfs.profile_read(0, "E")
+        got, ref = run(d, d["m"])
+        n = nfs.profile_read(0, "E")[0]
+    finally:
+        nfs.profile_enable(0, False)
+    e = per_term(got, ref)
+    print(f"grad_kcoef G={G} P={P}: {n} E launches, worst term {e.max():.1e}")
+    assert n == encodes and e.max() < BAR
