@@ -255,6 +255,7 @@ hipError_t launch_dft_axis(const float2* in, float2* out, int64_t outer, int n, 
 // in == out is allowed.
 struct DftPlan {
   int n, n1, n2, lw;      // lw: log2 of a workgroup's columns
+  int pitch;              // rows between the groups of n2 partial sums
   unsigned m, m1, m2;     // division by n, n1, n2
   bool two;
   int64_t blocks;

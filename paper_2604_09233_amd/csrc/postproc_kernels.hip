@@ -7,6 +7,8 @@
 // 1/L) with the last forward pass, then the inverse passes.  L (nx + ny + nz)
 // multiply-adds per direction instead of the L^2 of the grid's full DFT
 // matrix.
+#include <algorithm>
+
 #include "nfs_internal.h"
 
 namespace nfs {
@@ -110,7 +112,10 @@ __global__ __launch_bounds__(256) void dft_axis_kernel(const float2* __restrict_
 //   X[j] = sum_k2 A[j1][k2] w^(n1 j2 k2),   w = exp(sign 2 pi i / n).
 // A workgroup holds all n rows of its W = 2^lw columns, twice, in LDS, rows
 // apart by an odd number of values, so that loads along a line (contiguous
-// axis) meet no bank conflict.  The direct sums above read LDS 2 n times per
+// axis) meet no bank conflict; A's groups of n2 rows are p.pitch rows apart, so
+// that the second sum's do not either (n = 2048 = 32 x 64, one column a
+// workgroup: a call on 4x2048x4 169 -> 81 us, direct sums 180; on 2048x4x4
+// 169 -> 79, direct 152).  The direct sums above read LDS 2 n times per
 // output, which bounds them; these read it 2 (n1 + n2) times.  All reads of a
 // workgroup's columns come before its writes: in == out is allowed.
 // 96 x 96 x 48: the call 80 -> 45.5 us, error against 64 bits 5.7e-7 ->
@@ -123,7 +128,7 @@ __device__ __forceinline__ int div_magic(int x, unsigned m, int d) { return d ==
 
 __device__ __forceinline__ void dft_two_factors(const float2* tw, float2* a, float2* b, const DftPlan& p, int S,
                                                 float sg) {
-  const int n = p.n, n1 = p.n1, n2 = p.n2, nout = n << p.lw, cm = (1 << p.lw) - 1;
+  const int n = p.n, n1 = p.n1, n2 = p.n2, pad = p.pitch - n2, nout = n << p.lw, cm = (1 << p.lw) - 1;
   for (int e = threadIdx.x; e < nout; e += blockDim.x) {
     const int c = e & cm, r = e >> p.lw, j1 = div_magic(r, p.m2, n2), k2 = r - j1 * n2;
     float re = 0.f, im = 0.f;
@@ -142,14 +147,14 @@ __device__ __forceinline__ void dft_two_factors(const float2* tw, float2* a, flo
     }
     const float2 w = tw[j1 * k2];
     const float wy = sg * w.y;
-    b[r * S + c] = make_float2(fmaf(re, w.x, -im * wy), fmaf(re, wy, im * w.x));
+    b[(r + j1 * pad) * S + c] = make_float2(fmaf(re, w.x, -im * wy), fmaf(re, wy, im * w.x));
   }
   __syncthreads();
   for (int e = threadIdx.x; e < nout; e += blockDim.x) {
     const int c = e & cm, r = e >> p.lw, j2 = div_magic(r, p.m1, n1), j1 = r - j2 * n1;
     float re = 0.f, im = 0.f;
     int idx = 0;
-    const float2* x = b + j1 * n2 * S + c;
+    const float2* x = b + j1 * p.pitch * S + c;
 #pragma unroll 4
     for (int k2 = 0; k2 < n2; ++k2) {
       const float2 v = x[k2 * S], w = tw[idx];
@@ -174,7 +179,7 @@ __global__ __launch_bounds__(256) void dft_two_kernel(const float2* in, float2* 
   const int n = p.n, W = 1 << p.lw, S = W | 1;
   float2* tw = lds;             // [n]
   float2* a = lds + n;          // [n][S]
-  float2* b = a + (size_t)n * S;  // [n][S]
+  float2* b = a + (size_t)n * S;  // [n1][pitch][S]
   int64_t base, ncol;
   if (inner == 1) {
     base = (int64_t)blockIdx.x * W;
@@ -283,8 +288,8 @@ hipError_t launch_dft_axis(const float2* in, float2* out, int64_t outer, int n, 
 
 // Two factors nearest the root of n, and the columns of a workgroup: 16, fewer
 // until the pass has 1024 workgroups (calls of 96x96x48 / 219x219x22 at 256,
-// 512, 1024 and 2048: 57.9, 47.3, 46.0, 49.8 / 242, 166, 144, 142 us), but at
-// least one output per thread.
+// 512, 1024 and 2048: 57.9, 47.3, 46.0, 49.8 / 242, 166, 144, 142 us), but no
+// fewer than leave half the threads an output.
 // The rule: they are taken where they save half the direct sum's terms and one column's outputs,
 // in turns of a workgroup's 256 threads, take no more terms than the direct
 // kernel's one output per thread (few columns and a long axis such as 3 x 677).
@@ -298,15 +303,28 @@ DftPlan dft_plan(int n, int64_t outer, int64_t inner) {
   const int64_t sum = p.n1 + p.n2;
   p.two = 2 * sum <= n && cdiv(n, 256) * sum <= n;
   auto blocks = [&] { return inner == 1 ? cdiv(outer, (int64_t)1 << p.lw) : outer * cdiv(inner, (int64_t)1 << p.lw); };
-  auto slots = [&] { return n + 2 * (int64_t)n * ((1 << p.lw) | 1); };
+  auto slots = [&](int pitch) { return n + (n + (int64_t)p.n1 * pitch) * ((1 << p.lw) | 1); };
+  constexpr int kSlots = 65536 / 8;
   p.lw = 4;
-  while (p.lw > 0 && (slots() > 65536 / 8 || (blocks() < 1024 && (n << p.lw) > 256))) --p.lw;
+  while (p.lw > 0 && (slots(p.n2) > kSlots || (blocks() < 1024 && (n << p.lw) > 256))) --p.lw;
+  // rows between the groups of A: up to three more than n2, the fewest with the
+  // least 8-byte reads of 32 lanes (columns, then j1) on one of 32 banks
+  p.pitch = p.n2;
+  for (int q = p.n2, least = 33; p.two && q < p.n2 + 4 && slots(q) <= kSlots && least > 1; ++q) {
+    int hits[32] = {}, worst = 0;
+    for (int i = 0; i < 32 && (i >> p.lw) < p.n1; ++i)
+      worst = std::max(worst, ++hits[((i >> p.lw) * q * ((1 << p.lw) | 1) + (i & ((1 << p.lw) - 1))) % 32]);
+    if (worst < least) {
+      least = worst;
+      p.pitch = q;
+    }
+  }
   auto magic = [](int d) { return (unsigned)((((uint64_t)1 << 32) + d - 1) / d); };  // d >= 2 where used
   p.m = magic(n);
   p.m1 = magic(p.n1);
   p.m2 = magic(p.n2);
   p.blocks = blocks();
-  p.lds = (size_t)slots() * 8;
+  p.lds = (size_t)slots(p.pitch) * 8;
   return p;
 }
 
