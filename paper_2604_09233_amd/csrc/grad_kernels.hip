@@ -78,76 +78,9 @@ __device__ __forceinline__ float voxel_max(const float2* __restrict__ rho, const
   return mx;
 }
 
-// ve[l] = exponent of max_c |S_c rho|; em[b][x] = workgroup x's largest
-// exponent of |h_b| plus that of its voxel.  Maxima in registers, reduced once:
-// with an LDS atomic per voxel and term 36 us at 128x128, 16 coils, 16 terms.
-__global__ __launch_bounds__(256) void grad_range_kernel(const float2* __restrict__ rho,
-                                                         const float2* __restrict__ sens,
-                                                         const float* __restrict__ fields, int64_t L, int G, int P,
-                                                         int* __restrict__ ve, int* __restrict__ em) {
-  __shared__ int red[kWaves][kMaxTerms];
-  int mx[kMaxTerms];
-#pragma unroll
-  for (int b = 0; b < kMaxTerms; ++b) mx[b] = kNoExp;
-  for (int64_t l = (int64_t)blockIdx.x * 256 + threadIdx.x; l < L; l += (int64_t)gridDim.x * 256) {
-    const int e = top_exp(voxel_max(rho, sens, l, L, G));
-    ve[l] = e;
-#pragma unroll
-    for (int b = 0; b < kMaxTerms; ++b)
-      if (b < P) {
-        const int eh = top_exp(fabsf(fields[(int64_t)b * L + l]));
-        mx[b] = max(mx[b], e == kNoExp || eh == kNoExp ? kNoExp : e + eh);
-      }
-  }
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int b = 0; b < kMaxTerms; ++b)
-    if (b < P) {
-      for (int off = 32; off > 0; off >>= 1) mx[b] = max(mx[b], __shfl_xor(mx[b], off));
-      if (lane == 0) red[wave][b] = mx[b];
-    }
-  __syncthreads();
-  if ((int)threadIdx.x < P) {
-    int m = red[0][threadIdx.x];
-    for (int w = 1; w < kWaves; ++w) m = max(m, red[w][threadIdx.x]);
-    em[threadIdx.x * gridDim.x + blockIdx.x] = m;
-  }
-}
-
-// The voxels' operand; workgroup 0 also forms eb[b], the maximum of em[b].
-__global__ __launch_bounds__(256) void grad_pack_q_kernel(const float2* __restrict__ rho,
-                                                          const float2* __restrict__ sens, int64_t L, int G, int NK,
-                                                          int64_t LC, const int* __restrict__ ve,
-                                                          const int* __restrict__ em, int nem, int P,
-                                                          int* __restrict__ eb, h8* __restrict__ out) {
-  if (blockIdx.x == 0)
-    for (int b = threadIdx.x >> 6; b < P; b += kWaves) {
-      int mx = kNoExp;
-      for (int x = threadIdx.x & 63; x < nem; x += 64) mx = max(mx, em[b * nem + x]);
-      for (int off = 32; off > 0; off >>= 1) mx = max(mx, __shfl_xor(mx, off));
-      if ((threadIdx.x & 63) == 0) eb[b] = mx;
-    }
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= LC * NK * 64) return;
-  const int lane = (int)(i & 63), g = lane >> 4;
-  const int64_t blk = i >> 6, l = blk / NK * kChunk + (lane & 15);
-  const int kk = (int)(blk % NK);
-  const int e = l < L ? ve[l] : kNoExp, s = e == kNoExp ? 0 : kTop - e;
-  float v[8];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int c = kk * 16 + g * 4 + j;
-    float2 q = make_float2(0.f, 0.f);
-    if (l < L && c < G) q = cmul(sens[(int64_t)c * L + l], rho[l]);
-    v[2 * j] = ldexpf(q.x, s);
-    v[2 * j + 1] = ldexpf(q.y, s);
-  }
-  store_split(v, out, blk, lane);
-}
-
-__global__ __launch_bounds__(256) void grad_pack_G_kernel(const float2* __restrict__ gm, int64_t K, int G, int NK,
-                                                          int64_t KC, int* __restrict__ ge, h8* __restrict__ out) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+// The samples' operand (i: lane index over tiles x NK x 64).
+__device__ __forceinline__ void grad_pack_G(const float2* __restrict__ gm, int64_t K, int G, int NK, int64_t KC,
+                                            int* __restrict__ ge, h8* __restrict__ out, int64_t i) {
   if (i >= KC * NK * 64) return;
   const int lane = (int)(i & 63), g = lane >> 4;
   const int64_t blk = i >> 6, k = blk / NK * kChunk + (lane & 15);
@@ -179,10 +112,74 @@ __global__ __launch_bounds__(256) void grad_pack_G_kernel(const float2* __restri
   store_split(v, out, blk, lane);
 }
 
-__global__ __launch_bounds__(256) void grad_pack_h_kernel(const float* __restrict__ fields, int64_t L, int P, int NP,
-                                                          int64_t npair, const int* __restrict__ ve,
-                                                          const int* __restrict__ eb, h8* __restrict__ out) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+// The first nem workgroups: ve[l] = exponent of max_c |S_c rho|; em[b][x] =
+// workgroup x's largest exponent of |h_b| plus that of its voxel; the others
+// pack the samples' operand, which needs none of it (4 us as a launch by
+// itself).  Maxima in registers, reduced once: with an LDS atomic per voxel
+// and term 36 us at 128x128, 16 coils, 16 terms, 11 now.
+__global__ __launch_bounds__(256) void grad_range_pack_G_kernel(
+    const float2* __restrict__ rho, const float2* __restrict__ sens, const float* __restrict__ fields, int64_t L, int G,
+    int P, int nem, int* __restrict__ ve, int* __restrict__ em, const float2* __restrict__ gm, int64_t K, int NK,
+    int64_t KC, int* __restrict__ ge, h8* __restrict__ gf) {
+  if ((int)blockIdx.x >= nem) {
+    grad_pack_G(gm, K, G, NK, KC, ge, gf, (int64_t)(blockIdx.x - nem) * 256 + threadIdx.x);
+    return;
+  }
+  __shared__ int red[kWaves][kMaxTerms];
+  int mx[kMaxTerms];
+#pragma unroll
+  for (int b = 0; b < kMaxTerms; ++b) mx[b] = kNoExp;
+  for (int64_t l = (int64_t)blockIdx.x * 256 + threadIdx.x; l < L; l += (int64_t)nem * 256) {
+    const int e = top_exp(voxel_max(rho, sens, l, L, G));
+    ve[l] = e;
+#pragma unroll
+    for (int b = 0; b < kMaxTerms; ++b)
+      if (b < P) {
+        const int eh = top_exp(fabsf(fields[(int64_t)b * L + l]));
+        mx[b] = max(mx[b], e == kNoExp || eh == kNoExp ? kNoExp : e + eh);
+      }
+  }
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int b = 0; b < kMaxTerms; ++b)
+    if (b < P) {
+      for (int off = 32; off > 0; off >>= 1) mx[b] = max(mx[b], __shfl_xor(mx[b], off));
+      if (lane == 0) red[wave][b] = mx[b];
+    }
+  __syncthreads();
+  if ((int)threadIdx.x < P) {
+    int m = red[0][threadIdx.x];
+    for (int w = 1; w < kWaves; ++w) m = max(m, red[w][threadIdx.x]);
+    em[threadIdx.x * nem + blockIdx.x] = m;
+  }
+}
+
+// The voxels' operand (i: lane index over chunks x NK x 64).
+__device__ __forceinline__ void grad_pack_q(const float2* __restrict__ rho, const float2* __restrict__ sens, int64_t L,
+                                            int G, int NK, int64_t LC, const int* __restrict__ ve,
+                                            h8* __restrict__ out, int64_t i) {
+  if (i >= LC * NK * 64) return;
+  const int lane = (int)(i & 63), g = lane >> 4;
+  const int64_t blk = i >> 6, l = blk / NK * kChunk + (lane & 15);
+  const int kk = (int)(blk % NK);
+  const int e = l < L ? ve[l] : kNoExp, s = e == kNoExp ? 0 : kTop - e;
+  float v[8];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int c = kk * 16 + g * 4 + j;
+    float2 q = make_float2(0.f, 0.f);
+    if (l < L && c < G) q = cmul(sens[(int64_t)c * L + l], rho[l]);
+    v[2 * j] = ldexpf(q.x, s);
+    v[2 * j + 1] = ldexpf(q.y, s);
+  }
+  store_split(v, out, blk, lane);
+}
+
+// The fields' operand (i: lane index over pairs x NP x 64); eb[b]: the
+// exponent of term b's largest field value times voxel magnitude.
+__device__ __forceinline__ void grad_pack_h(const float* __restrict__ fields, int64_t L, int P, int NP, int64_t npair,
+                                            const int* __restrict__ ve, const int* eb, h8* __restrict__ out,
+                                            int64_t i) {
   if (i >= npair * NP * 64) return;
   const int lane = (int)(i & 63), g = lane >> 4;
   const int64_t blk = i >> 6, pair = blk / NP;
@@ -196,6 +193,31 @@ __global__ __launch_bounds__(256) void grad_pack_h_kernel(const float* __restric
     v[e] = s == kNoExp ? 0.f : ldexpf(fields[(int64_t)b * L + l], s + kTop - top);
   }
   store_split(v, out, blk, lane);
+}
+
+// The first nh workgroups pack the fields, each with its own maxima of em (a
+// few kB from the L2, against a launch that forms eb before this one), the
+// others the voxels; the first one keeps eb for the finish.
+__global__ __launch_bounds__(256) void grad_pack_hq_kernel(
+    const float2* __restrict__ rho, const float2* __restrict__ sens, const float* __restrict__ fields, int64_t L, int G,
+    int P, int NK, int NP, int64_t LC, int64_t npair, const int* __restrict__ ve, const int* __restrict__ em, int nem,
+    int64_t nh, int* __restrict__ eb, h8* __restrict__ q, h8* __restrict__ hf) {
+  if ((int64_t)blockIdx.x >= nh) {
+    grad_pack_q(rho, sens, L, G, NK, LC, ve, q, (blockIdx.x - nh) * 256 + threadIdx.x);
+    return;
+  }
+  __shared__ int top[kMaxTerms];
+  for (int b = threadIdx.x >> 6; b < P; b += kWaves) {
+    int mx = kNoExp;
+    for (int x = threadIdx.x & 63; x < nem; x += 64) mx = max(mx, em[b * nem + x]);
+    for (int off = 32; off > 0; off >>= 1) mx = max(mx, __shfl_xor(mx, off));
+    if ((threadIdx.x & 63) == 0) {
+      top[b] = mx;
+      if (blockIdx.x == 0) eb[b] = mx;
+    }
+  }
+  __syncthreads();
+  grad_pack_h(fields, L, P, NP, npair, ve, top, hf, (int64_t)blockIdx.x * 256 + threadIdx.x);
 }
 
 // Grid (ceil(HC / (kWaves MT)), nsplit), held samples x streamed pairs of
@@ -341,7 +363,7 @@ __global__ __launch_bounds__(256) void grad_kcoef_finish_kernel(const float* __r
 // ---------------------------------------------------------------------------
 static int grad_nk(int G) { return G <= 16 ? 1 : G <= 32 ? 2 : 4; }
 static int grad_np(int P) { return P <= 16 ? 1 : 2; }
-// workgroups of grad_range_kernel
+// workgroups that take the voxels in grad_range_pack_G_kernel
 static int grad_range_blocks(int64_t L) { return (int)std::min<int64_t>(cdiv(L, 256), kBmaxBlocks); }
 // held tiles per wave: the samples' operands take 16 NK registers a tile
 static int grad_mt(int G) { return grad_nk(G) <= 2 ? 2 : 1; }
@@ -411,13 +433,11 @@ hipError_t launch_grad_kcoef_fused(const GradShape& g, const void* heldcoef, con
   int *ve = (int*)(w + g.o_ve), *em = (int*)(w + g.o_em), *eb = (int*)(w + g.o_eb), *ge = (int*)(w + g.o_gs);
   const int nem = grad_range_blocks(L);
   auto blocks = [](int64_t n) { return dim3((unsigned)cdiv(n, 256)); };
-  hipLaunchKernelGGL(grad_range_kernel, dim3(nem), dim3(256), 0, s, rho, sens, fields, L, G, P, ve, em);
-  hipLaunchKernelGGL(grad_pack_q_kernel, blocks(LC * g.NK * 64), dim3(256), 0, s, rho, sens, L, G, g.NK, LC, ve, em,
-                     nem, P, eb, (h8*)(w + g.o_q));
-  hipLaunchKernelGGL(grad_pack_G_kernel, blocks(KC * g.NK * 64), dim3(256), 0, s, grad_m, K, G, g.NK, KC, ge,
-                     (h8*)(w + g.o_G));
-  hipLaunchKernelGGL(grad_pack_h_kernel, blocks(g.npair * g.NP * 64), dim3(256), 0, s, fields, L, P, g.NP, g.npair, ve,
-                     eb, (h8*)(w + g.o_h));
+  hipLaunchKernelGGL(grad_range_pack_G_kernel, dim3((unsigned)(nem + cdiv(KC * g.NK * 64, 256))), dim3(256), 0, s, rho,
+                     sens, fields, L, G, P, nem, ve, em, grad_m, K, g.NK, KC, ge, (h8*)(w + g.o_G));
+  const int64_t nh = cdiv(g.npair * g.NP * 64, 256);
+  hipLaunchKernelGGL(grad_pack_hq_kernel, dim3((unsigned)(nh + cdiv(LC * g.NK * 64, 256))), dim3(256), 0, s, rho, sens,
+                     fields, L, G, P, g.NK, g.NP, LC, g.npair, ve, em, nem, nh, eb, (h8*)(w + g.o_q), (h8*)(w + g.o_h));
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   float* part = (float*)(w + g.o_part);
