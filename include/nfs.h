@@ -430,7 +430,8 @@ int nfs_set_shape(nfs_ctx* ctx, const nfs_problem* prob, int precision, int op, 
  * real, grad_kcoef: [K][P] real -- each output may be NULL to skip it.
  * Cost: one E^H for grad_rho, one for grad_b0; for grad_kcoef in FP32 one
  * pass about the cost of one E, in FP16 and BF16 one E per field term with
- * as many terms per launch as fit 64 virtual coils.  Workspace: nfs_workspace_bytes(NFS_OP_EHE).                 */
+ * as many terms per launch as fit 64 virtual coils and the workspace.
+ * Workspace: nfs_workspace_bytes(NFS_OP_EHE).                               */
 int nfs_encode_backward(nfs_ctx* ctx, const nfs_problem* prob, const float* rho, const float* grad_m,
                         float* grad_rho, float* grad_b0, float* grad_kcoef, int precision,
                         void* ws, size_t ws_bytes, void* stream);

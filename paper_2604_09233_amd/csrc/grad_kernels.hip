@@ -222,6 +222,10 @@ __global__ __launch_bounds__(256) void grad_pack_hq_kernel(
 
 // Grid (ceil(HC / (kWaves MT)), nsplit), held samples x streamed pairs of
 // voxel chunks, staged through LDS and remapped to XCDs as in encode_kernel.
+// 128x128, 60 000 samples, 16 coils, 16 terms: 553 us, matrix cores 43 %
+// (1082 TFLOP/s), sines and cosines 18 % and the other VALU work 43 % of their
+// peaks; no LDS conflicts.  They share the issue slots; w's factor is one of
+// about eight VALU operations per value and is not seen in the time.
 template <int NQ, int NK, int NP, int MT, bool FRACT>
 __device__ __forceinline__ void grad_stream(const u4* __restrict__ strmcoef, const u4* __restrict__ q,
                                             const u4* __restrict__ hf, float wscale, int64_t p0, int64_t p1, int64_t LC,
